@@ -15,6 +15,8 @@
 // near field uses the float32 input coordinates directly (x - y of two close
 // float32 values is exact). Per-target sums are accumulated per LDS tile in
 // float32 and folded into a (hi, lo) pair with Knuth's TwoSum.
+#include <algorithm>
+#include <limits>
 #include <type_traits>
 
 #include "nbody.hpp"
@@ -490,48 +492,215 @@ __global__ __launch_bounds__(64) void k_eval(EvalArgs a, SurfaceGeom g, PointSrc
 }
 
 // ------------------------------------------------------------ all pairs
-__global__ __launch_bounds__(256) void k_direct(const float *trg, int64_t n_trg, const float *src, const float *nrm,
-                                               int64_t n_src, const float *q, const float *mu, float delta2,
-                                               float *pot, float *field) {
-    __shared__ float sh[256][8];
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const bool valid = i < n_trg;
-    const float x = valid ? trg[3 * i] : 0.f, y = valid ? trg[3 * i + 1] : 0.f, z = valid ? trg[3 * i + 2] : 0.f;
-    float hp = 0.f, lp = 0.f, hf[3] = {0.f, 0.f, 0.f}, lf[3] = {0.f, 0.f, 0.f};
-    for (int64_t j0 = 0; j0 < n_src; j0 += 256) {
-        const int64_t j = j0 + threadIdx.x;
-        if (j < n_src) {
-            sh[threadIdx.x][0] = src[3 * j];
-            sh[threadIdx.x][1] = src[3 * j + 1];
-            sh[threadIdx.x][2] = src[3 * j + 2];
-            sh[threadIdx.x][3] = q ? q[j] : 0.f;
-            float m = mu ? mu[j] : 0.f;
-            sh[threadIdx.x][4] = mu ? m * nrm[3 * j] : 0.f;
-            sh[threadIdx.x][5] = mu ? m * nrm[3 * j + 1] : 0.f;
-            sh[threadIdx.x][6] = mu ? m * nrm[3 * j + 2] : 0.f;
-        }
-        __syncthreads();
-        const int cnt = (int)min((int64_t)256, n_src - j0);
-        float pp = 0.f, pf[3] = {0.f, 0.f, 0.f};
-        for (int jj = 0; jj < cnt; ++jj) {
-            float dx = x - sh[jj][0], dy = y - sh[jj][1], dz = z - sh[jj][2];
-            float r2 = dx * dx + dy * dy + dz * dz;
-            float inv = (r2 >= delta2 && r2 > 0.f) ? rsq(r2) : 0.f;
-            float inv3 = inv * inv * inv;
-            float qq = sh[jj][3];
-            pp += qq * inv + (sh[jj][4] * dx + sh[jj][5] * dy + sh[jj][6] * dz) * inv3;
-            pf[0] += qq * inv3 * dx;
-            pf[1] += qq * inv3 * dy;
-            pf[2] += qq * inv3 * dz;
-        }
-        two_sum_into(hp, lp, pp);
-        for (int c = 0; c < 3; ++c) two_sum_into(hf[c], lf[c], pf[c]);
-        __syncthreads();
+//
+// Bound: VALU issue, 15-16 instructions a pair (3 subtractions, 3 for r^2,
+// v_rsq, the exclusion's compare and select, 1/r^2, 3 + 2 for the double
+// layer), as long as the chip is full. A workgroup of 16 waves owns
+// T = TPL << lgL targets and runs all sources: thread (s, tl) holds the TPL
+// targets tl + u L (L = 1 << lgL <= 64 lanes) and takes the staged sources
+// s, s + S, ... of every tile (S = 1024 / L slices), so that a few thousand
+// targets, or a few hundred, still fill 256 CUs; the slices are summed across
+// lanes, then across waves through LDS, in a fixed order and without scratch
+// memory. The next tile's values load while the current one is used. Tiles
+// are 1024 sources in two buffers (one barrier a tile), or with one target
+// per lane 4096 in one: the few pairs of a 1024-tile then end before the next
+// one's loads do (300 targets, 300,000 sources: 237 -> 126 us). Records are one
+// (single layer) or two float4 in separate arrays, so that lanes of different
+// slices read consecutive 16-byte slots. Kernels for the potential of the
+// single layer, of the double layer (with or without the single) and for the
+// field (with the potential) leave out the other's arithmetic.
+// Float32 sums of at most 64 sources are folded into (hi, lo) pairs.
+// Measured against one thread per target, workgroups of 256 and every output
+// computed: 801 x 801 52 -> 8.5 us (a launch), 300 x 300,000 single layer
+// 18,990 -> 126 us, 4000 x 1M both layers 64,440 -> 1,980 us (2.0e12 pairs/s,
+// 0.82 of 3.93e13 lane-instructions/s at 16 a pair), 60,000 x 60,000 single
+// layer 3,720 -> 1,020 us.
+constexpr int kDirThreads = 1024;
+
+template <bool DL, bool FIELD, int TPL, int KS>
+__global__ __launch_bounds__(kDirThreads) void k_direct(const float *trg, int64_t n_trg, const float *src,
+                                                       const float *nrm, int64_t n_src, const float *q,
+                                                       const float *mu, float delta2, int lgL, float *pot,
+                                                       float *field) {
+    constexpr int NOUT = FIELD ? 4 : 1, NREC = DL ? 2 : 1, NW = kDirThreads / 64;
+    constexpr int TILE = KS * kDirThreads, NBUF = KS == 1 ? 2 : 1;
+    constexpr int NTILE = NBUF * NREC * TILE * 4, NRED = NW * 64 * TPL * NOUT * 2;
+    __shared__ __align__(16) float sh[NTILE > NRED ? NTILE : NRED];
+    float4 *rec = (float4 *)sh;  // [buffer][record part][source of the tile]
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int L = 1 << lgL, S = kDirThreads >> lgL, s = t >> lgL, tl = t & (L - 1);
+    const int64_t t0 = (int64_t)blockIdx.x * (TPL * L);
+    float x[TPL], y[TPL], z[TPL], hi[TPL][NOUT], lo[TPL][NOUT], part[TPL][NOUT];
+#pragma unroll
+    for (int u = 0; u < TPL; ++u) {
+        const int64_t i = min(t0 + tl + u * L, n_trg - 1);
+        x[u] = trg[3 * i];
+        y[u] = trg[3 * i + 1];
+        z[u] = trg[3 * i + 2];
+#pragma unroll
+        for (int o = 0; o < NOUT; ++o) hi[u][o] = lo[u][o] = part[u][o] = 0.f;
     }
-    if (!valid) return;
-    if (pot) pot[i] = (hp + lp) * kInv4Pi;
-    if (field)
-        for (int c = 0; c < 3; ++c) field[3 * i + c] = (hf[c] + lf[c]) * kInv4Pi;
+    float4 r0[KS], r1[KS];
+    auto load = [&](int64_t j0) {
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const int64_t j = j0 + k * kDirThreads + t;
+            r0[k] = make_float4((float)kFar, (float)kFar, (float)kFar, 0.f);  // past the end: no strength, far away
+            r1[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (j < n_src) {
+                r0[k].x = src[3 * j];
+                r0[k].y = src[3 * j + 1];
+                r0[k].z = src[3 * j + 2];
+                r0[k].w = q ? q[j] : 0.f;
+                if (DL) {
+                    r1[k].x = nrm[3 * j];
+                    r1[k].y = nrm[3 * j + 1];
+                    r1[k].z = nrm[3 * j + 2];
+                    r1[k].w = mu[j];
+                }
+            }
+        }
+    };
+    auto stage = [&](float4 *a, float4 *b) {
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            // a coordinate that is not finite makes every sum NaN, also where 1/r alone would give 0
+            r0[k].w += 0.f * r0[k].x + 0.f * r0[k].y + 0.f * r0[k].z;
+            a[k * kDirThreads + t] = r0[k];
+            if (DL) b[k * kDirThreads + t] = make_float4(r1[k].w * r1[k].x, r1[k].w * r1[k].y, r1[k].w * r1[k].z, 0.f);
+        }
+    };
+    auto fold = [&] {
+#pragma unroll
+        for (int u = 0; u < TPL; ++u)
+#pragma unroll
+            for (int o = 0; o < NOUT; ++o) {
+                two_sum_into(hi[u][o], lo[u][o], part[u][o]);
+                part[u][o] = 0.f;
+            }
+    };
+    load(0);
+    int buf = 0, held = 0;
+    for (int64_t j0 = 0; j0 < n_src; j0 += TILE, buf ^= NBUF - 1) {
+        float4 *a = rec + buf * NREC * TILE, *b = a + TILE;
+        if (NBUF == 1) __syncthreads();  // every wave is done with the tile before
+        stage(a, b);
+        __syncthreads();  // the tile is staged (with two buffers: and the one before no longer read)
+        if (j0 + TILE < n_src) load(j0 + TILE);
+        const int cnt = (int)min((int64_t)TILE, n_src - j0);
+        const int niter = (cnt + S - 1) >> (10 - lgL);  // sources per slice, at most KS L
+        for (int i = 0; i < niter; ++i) {
+            const float4 v = a[s + i * S];
+            float4 m;
+            if (DL) m = b[s + i * S];
+#pragma unroll
+            for (int u = 0; u < TPL; ++u) {
+                const float dx = x[u] - v.x, dy = y[u] - v.y, dz = z[u] - v.z;
+                const float r2 = dx * dx + dy * dy + dz * dz;
+                float inv = rsq(r2);
+                inv = r2 < delta2 ? 0.f : inv;
+                const float inv2 = inv * inv;
+                if constexpr (FIELD) {
+                    const float qi = v.w * inv, di3 = qi * inv2;
+                    part[u][0] += qi;
+                    part[u][1] += di3 * dx;
+                    part[u][2] += di3 * dy;
+                    part[u][3] += di3 * dz;
+                } else {
+                    float w = v.w;
+                    if (DL) w += (m.x * dx + m.y * dy + m.z * dz) * inv2;
+                    part[u][0] += w * inv;
+                }
+            }
+        }
+        held += niter;
+        if (held + KS * L > 64) {
+            fold();
+            held = 0;
+        }
+    }
+    fold();
+    // slices of one wave: lanes that differ in the bits above L
+    for (int o = L; o < 64; o <<= 1)
+#pragma unroll
+        for (int u = 0; u < TPL; ++u)
+#pragma unroll
+            for (int c = 0; c < NOUT; ++c) {
+                const float h = __shfl_xor(hi[u][c], o), l = __shfl_xor(lo[u][c], o);
+                two_sum_into(hi[u][c], lo[u][c], h);
+                lo[u][c] += l;
+            }
+    __syncthreads();  // the tiles are no longer read
+    const int nt = TPL * L;
+    if (lane < L)
+#pragma unroll
+        for (int u = 0; u < TPL; ++u)
+#pragma unroll
+            for (int c = 0; c < NOUT; ++c) {
+                float *p = sh + 2 * ((wave * NOUT + c) * nt + u * L + lane);
+                p[0] = hi[u][c];
+                p[1] = lo[u][c];
+            }
+    __syncthreads();
+    const int64_t i = t0 + t;
+    if (t >= nt || i >= n_trg) return;
+    // as for the sources: 0, or NaN for a target that is not finite
+    const float nf = n_src > 0 ? 0.f * trg[3 * i] + 0.f * trg[3 * i + 1] + 0.f * trg[3 * i + 2] : 0.f;
+#pragma unroll
+    for (int c = 0; c < NOUT; ++c) {
+        float h = 0.f, l = 0.f;
+        for (int w = 0; w < NW; ++w) {
+            const float *p = sh + 2 * ((w * NOUT + c) * nt + t);
+            two_sum_into(h, l, p[0]);
+            l += p[1];
+        }
+        const float v = (h + l) * kInv4Pi + nf;
+        if (c == 0) {
+            if (pot) pot[i] = v;
+        } else if (field) {
+            field[3 * i + c - 1] = v;
+        }
+    }
+}
+
+template <bool DL, bool FIELD>
+void launch_direct(const float *trg, int64_t n_trg, const float *src, const float *nrm, int64_t n_src, const float *q,
+                   const float *mu, float delta2, float *pot, float *field, hipStream_t s) {
+    // Targets per workgroup T = TPL << lg by a fit of the measured times: a
+    // round of 256 workgroups (one per CU) costs T plus about 5.6 for staging
+    // and latency, which two resident workgroups share. (300,000 sources,
+    // single layer, one round: T = 4 169 us, 8 232, 16 385.) More targets per
+    // lane read each staged record from LDS fewer times, hence the weights,
+    // which only decide between splits of the same T; ties go to the larger T.
+    constexpr int kTplMax = FIELD ? 2 : 4;
+    int tpl = 1, lg = 0;
+    double best = 1e300;
+    for (int c = kTplMax; c >= 1; c >>= 1)
+        for (int l = 6; l >= 0; --l) {
+            if (c > 1 && l < 2) continue;  // fewer than four lanes a slice: one target per lane instead
+            const int64_t T = (int64_t)c << l, wg = (n_trg + T - 1) / T;
+            const int64_t rounds = (wg + 255) / 256;
+            const double cost = (double)rounds * (double)T * (c >= 4 ? 1.0 : c == 2 ? 1.02 : 1.05) +
+                                5.6 * (double)((rounds + 1) / 2);
+            if (cost < best) {
+                best = cost;
+                tpl = c;
+                lg = l;
+            }
+        }
+    const int64_t T = (int64_t)tpl << lg;
+    const dim3 g((unsigned)((n_trg + T - 1) / T)), b(kDirThreads);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, g, b, 0, s, trg, n_trg, src, nrm, n_src, q, mu, delta2, lg, pot, field);
+    };
+    if constexpr (kTplMax == 4)
+        if (tpl == 4) return go(k_direct<DL, FIELD, 4, 1>);
+    if (tpl == 2)
+        go(k_direct<DL, FIELD, 2, 1>);
+    else if (lg <= 4 && n_src > kDirThreads)
+        go(k_direct<DL, FIELD, 1, 4>);
+    else
+        go(k_direct<DL, FIELD, 1, 1>);
 }
 
 }  // namespace
@@ -585,9 +754,15 @@ void eval_leaves(int nrhs, bool sl, bool dl, const EvalArgs &a, const SurfaceGeo
 
 void direct_all_pairs(const float *trg, int64_t n_trg, const float *src, const float *nrm, int64_t n_src,
                       const float *q, const float *mu, float delta, float *pot, float *field, hipStream_t s) {
-    if (n_trg <= 0) return;
-    hipLaunchKernelGGL(k_direct, dim3(grid_for(n_trg, 256)), dim3(256), 0, s, trg, n_trg, src, nrm, n_src, q, mu,
-                       delta * delta, pot, field);
+    if (n_trg <= 0 || (!pot && !field)) return;
+    // pairs with r^2 < delta^2 and pairs at r = 0 are left out: one test against the larger bound
+    const float delta2 = std::max(delta * delta, std::numeric_limits<float>::denorm_min());
+    if (field)
+        launch_direct<false, true>(trg, n_trg, src, nrm, n_src, q, nullptr, delta2, pot, field, s);
+    else if (mu)
+        launch_direct<true, false>(trg, n_trg, src, nrm, n_src, q, mu, delta2, pot, nullptr, s);
+    else
+        launch_direct<false, false>(trg, n_trg, src, nrm, n_src, q, nullptr, delta2, pot, nullptr, s);
     FMM_HIP(hipGetLastError());
 }
 
