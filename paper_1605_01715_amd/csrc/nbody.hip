@@ -146,17 +146,18 @@ __global__ __launch_bounds__(64) void k_points_to_surface(const int32_t *items, 
 
 // ------------------------------------------------------------ leaf evaluation
 //
-// One wave per work item (up to 64 targets of a leaf). Lanes are laid out as
-// S source slices x L lane-targets, each lane holding TPL targets (1 to 4
-// with one output and one right-hand side, else 1 or 2), chosen per item to
-// keep most lane-slots busy: a 45-target item runs as 15 lanes x 3 targets x
-// 4 slices (94% of the slots) instead of 45 of 64 lanes, or 23 x 2 x 2 (70%).
-// More targets per lane also read each staged source once for more pairs.
-// Sources are staged in
-// LDS 64 at a time (records padded to 16 bytes, the tail of a tile filled
-// with zero-density sources far away), so the loop over a tile has the same
-// trip count in every lane and no per-pair validity test. Slices are summed
-// through LDS at the end.
+// One workgroup per work item (up to 64 targets of a leaf), of one wave or
+// of 2, 4 or 8 that share the item's sources (EvalArgs.waves). In a wave,
+// lanes are laid out as S source slices x L lane-targets, each lane holding
+// TPL targets (1 to 4 with one output and one right-hand side, else 1 or 2),
+// chosen per item to keep most lane-slots busy: a 45-target item runs as 15
+// lanes x 3 targets x 4 slices (94% of the slots) instead of 45 of 64 lanes,
+// or 23 x 2 x 2 (70%). More targets per lane also read each staged source once
+// for more pairs. Sources are staged in the wave's own part of LDS 64 at a
+// time (records padded to 16 bytes, the tail of a tile filled with
+// zero-density sources far away), so the loop over a tile has the same trip
+// count in every lane, no per-pair validity test and no barrier. Slices, then
+// waves, are summed through LDS at the end, in a fixed order.
 constexpr int kFar = 1000000000;  // far-away coordinate of padding records (1e9)
 
 template <int NRHS, bool SL, bool DL, bool FIELD>
@@ -168,12 +169,25 @@ struct EvalShape {
     static constexpr int NREC = 128;                                      // 64 + room for slice overrun
 };
 
-template <int TPL, int NRHS, bool SL, bool DL, bool FIELD>
+// Orders this wave's LDS writes before its later LDS reads (and the reverse):
+// one wave's LDS operations complete in order, so only the compiler must not
+// move them.
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The wave's share of an item; sh_all: the workgroup's LDS, NSH floats for
+// each wave. MW: the workgroup has several waves (a kernel of its own: the
+// share's bookkeeping spills scalar registers, 1.4% of a 300,000-point apply).
+template <int TPL, int NRHS, bool SL, bool DL, bool FIELD, bool MW, int NSH>
 __device__ void eval_item(const EvalArgs &a, const SurfaceGeom &g, const PointSrc &src, int leaf, int64_t t_first,
-                          int nt, float *sh, float *red) {
+                          int nt, float *sh_all) {
+    const int w = MW ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0, nw = MW ? blockDim.x >> 6 : 1;
     using E = EvalShape<NRHS, SL, DL, FIELD>;
-    constexpr int NOUT = E::NOUT, W = E::W, NREC = E::NREC;
-    const int lane = threadIdx.x;
+    constexpr int NOUT = E::NOUT, W = E::W;
+    const int lane = threadIdx.x & 63;
+    float *sh = sh_all + (size_t)w * NSH;
     const int L = (nt + TPL - 1) / TPL;      // lanes per slice
     const int S = 64 / L;                    // slices
     const int slice = lane / L, tl = lane % L;
@@ -208,6 +222,7 @@ __device__ void eval_item(const EvalArgs &a, const SurfaceGeom &g, const PointSr
     };
     pad(64 + lane);
 
+    int turn = 0;
     // surfaces: L2P (own downward equivalent density) and M2P (W-list boxes);
     // surface points never coincide with targets (they lie outside the box)
     for (int e = a.soff[leaf]; e < a.soff[leaf + 1]; ++e) {
@@ -218,6 +233,7 @@ __device__ void eval_item(const EvalArgs &a, const SurfaceGeom &g, const PointSr
         const double ox = g.centre[3 * box] - cx, oy = g.centre[3 * box + 1] - cy, oz = g.centre[3 * box + 2] - cz;
         const float *phi = (down ? a.phi_d : a.phi_u) + (int64_t)box * NRHS * g.n_pad;
         for (int m0 = 0; m0 < g.ns; m0 += 64) {
+            if (MW && turn++ % nw != w) continue;  // the item's surface tiles in turn
             const int m = m0 + lane;
             if (m < g.ns) {
                 float *p = sh + lane * W;
@@ -228,7 +244,7 @@ __device__ void eval_item(const EvalArgs &a, const SurfaceGeom &g, const PointSr
             } else {
                 pad(lane);
             }
-            __syncthreads();
+            wave_sync();
             float part[TPL][NRHS][NOUT];
 #pragma unroll
             for (int u = 0; u < TPL; ++u)
@@ -267,7 +283,7 @@ __device__ void eval_item(const EvalArgs &a, const SurfaceGeom &g, const PointSr
             for (int u = 0; u < TPL; ++u)
                 for (int r = 0; r < NRHS; ++r)
                     for (int o = 0; o < NOUT; ++o) two_sum_into(hi[u][r][o], lo[u][r][o], part[u][r][o]);
-            __syncthreads();
+            wave_sync();
         }
     }
 
@@ -288,10 +304,28 @@ __device__ void eval_item(const EvalArgs &a, const SurfaceGeom &g, const PointSr
     // past the last range stay inside it).
     const int32_t __attribute__((address_space(4))) *rng =
         (const int32_t __attribute__((address_space(4))) *)a.prng;
-    auto stream = [&](auto test_tag, int e0, int e1) {
+    auto stream = [&](auto test_tag, int e0, int e1, int rank) {
         constexpr bool TEST = decltype(test_tag)::value;
-        int e = e0, off = 0;
+        int e = e0, off = 0, left = 0x7fffffff;  // tiles left for this wave
+        if (MW && e0 < e1) {
+            // a contiguous share of the sequence's tiles for each wave (whole
+            // tiles apart from the sequence's last), found from the running
+            // counts, 64 ranges at a time
+            const int c0 = a.pcum[e0];
+            const int ntile = (a.pcum[e1 - 1] - c0 + rng[2 * e1 - 1] - rng[2 * e1 - 2] + 63) / 64;
+            const int at = ntile * rank / nw;
+            left = ntile * (rank + 1) / nw - at;
+            for (int k = e0; k < e1; k += 64) {
+                const bool below = k + lane < e1 && a.pcum[min(k + lane, e1 - 1)] - c0 <= 64 * at;
+                const int nbelow = __popcll(__ballot(below));
+                if (nbelow == 0) break;
+                e = k + nbelow - 1;
+            }
+            e = __builtin_amdgcn_readfirstlane(e);
+            off = 64 * at - (a.pcum[e] - c0);
+        }
         while (e < e1) {
+            if (MW && left-- <= 0) break;
             // this lane's source: the tile covers the rest of range e and,
             // past its end, the next ranges (a tile rarely spans more than four)
             int j = -1;
@@ -332,7 +366,7 @@ __device__ void eval_item(const EvalArgs &a, const SurfaceGeom &g, const PointSr
             } else {
                 pad(lane);
             }
-            __syncthreads();
+            wave_sync();
             float part[TPL][NRHS][NOUT];
 #pragma unroll
             for (int u = 0; u < TPL; ++u)
@@ -385,7 +419,7 @@ __device__ void eval_item(const EvalArgs &a, const SurfaceGeom &g, const PointSr
             for (int u = 0; u < TPL; ++u)
                 for (int r = 0; r < NRHS; ++r)
                     for (int o = 0; o < NOUT; ++o) two_sum_into(hi[u][r][o], lo[u][r][o], part[u][r][o]);
-            __syncthreads();
+            wave_sync();
             // advance the position by 64 sources
             int adv = 64;
             while (e < e1) {
@@ -402,14 +436,13 @@ __device__ void eval_item(const EvalArgs &a, const SurfaceGeom &g, const PointSr
     };
     if (a.points) {
         const int pmid = a.pmid ? a.pmid[leaf] : a.poff[leaf + 1];
-        stream(std::true_type{}, a.poff[leaf], pmid);
-        stream(std::false_type{}, pmid, a.poff[leaf + 1]);
+        stream(std::true_type{}, a.poff[leaf], pmid, w);
+        stream(std::false_type{}, pmid, a.poff[leaf + 1], nw - 1 - w);
     }
 
-    // sum the slices of each target through LDS, then slice 0 writes
+    // sum the slices of each target through the wave's LDS
     constexpr int NV = TPL * NRHS * NOUT;
-    if (active && slice > 0) {
-        float *q = red + (size_t)lane * NV * 2;
+    auto put = [&](float *q) {
         int v = 0;
 #pragma unroll
         for (int u = 0; u < TPL; ++u)
@@ -418,20 +451,31 @@ __device__ void eval_item(const EvalArgs &a, const SurfaceGeom &g, const PointSr
                     q[2 * v] = hi[u][r][o];
                     q[2 * v + 1] = lo[u][r][o];
                 }
-    }
-    __syncthreads();
-    if (active && slice == 0) {
-        for (int sl2 = 1; sl2 < S; ++sl2) {
-            const float *q = red + (size_t)(sl2 * L + tl) * NV * 2;
-            int v = 0;
+    };
+    auto add = [&](const float *q) {
+        int v = 0;
 #pragma unroll
-            for (int u = 0; u < TPL; ++u)
-                for (int r = 0; r < NRHS; ++r)
-                    for (int o = 0; o < NOUT; ++o, ++v) {
-                        two_sum_into(hi[u][r][o], lo[u][r][o], q[2 * v]);
-                        lo[u][r][o] += q[2 * v + 1];
-                    }
-        }
+        for (int u = 0; u < TPL; ++u)
+            for (int r = 0; r < NRHS; ++r)
+                for (int o = 0; o < NOUT; ++o, ++v) {
+                    two_sum_into(hi[u][r][o], lo[u][r][o], q[2 * v]);
+                    lo[u][r][o] += q[2 * v + 1];
+                }
+    };
+    if (active && slice > 0) put(sh + (size_t)lane * NV * 2);
+    wave_sync();
+    if (active && slice == 0)
+        for (int sl2 = 1; sl2 < S; ++sl2) add(sh + (size_t)(sl2 * L + tl) * NV * 2);
+    if constexpr (MW) {
+        // the other waves' sums, added by wave 0 in their order
+        wave_sync();
+        if (w > 0 && lane < L) put(sh + (size_t)lane * NV * 2);
+        __syncthreads();
+        if (w > 0) return;
+        if (lane < L)
+            for (int w2 = 1; w2 < nw; ++w2) add(sh_all + (size_t)w2 * NSH + (size_t)lane * NV * 2);
+    }
+    if (active && slice == 0) {
 #pragma unroll
         for (int u = 0; u < TPL; ++u) {
             const int t = tl + u * L;
@@ -457,14 +501,21 @@ __device__ void eval_item(const EvalArgs &a, const SurfaceGeom &g, const PointSr
 }
 
 template <int NRHS, bool SL, bool DL, bool FIELD>
-__global__ __launch_bounds__(64) void k_eval(EvalArgs a, SurfaceGeom g, PointSrc src) {
+struct EvalLds {
     using E = EvalShape<NRHS, SL, DL, FIELD>;
     // up to 4 targets per lane where one output and one right-hand side
     // keep the accumulators few; 2 otherwise
-    constexpr int MAXTPL = (E::NOUT == 1 && NRHS == 1) ? 4 : 2;
-    constexpr int NSH = E::NREC * E::W, NRED = 64 * MAXTPL * NRHS * E::NOUT * 2;
-    // the slice sums of the end reuse the source records' LDS
-    __shared__ __align__(16) float sh[NSH > NRED ? NSH : NRED];
+    static constexpr int MAXTPL = (E::NOUT == 1 && NRHS == 1) ? 4 : 2;
+    // floats per wave; the sums of the end reuse the source records' space
+    static constexpr int NSH = E::NREC * E::W, NRED = 64 * MAXTPL * NRHS * E::NOUT * 2;
+    static constexpr int N = NSH > NRED ? NSH : NRED;
+};
+
+template <int NRHS, bool SL, bool DL, bool FIELD, bool MW>
+__global__ __launch_bounds__(MW ? 64 * kEvalMaxWaves : 64) void k_eval(EvalArgs a, SurfaceGeom g, PointSrc src) {
+    using M = EvalLds<NRHS, SL, DL, FIELD>;
+    constexpr int MAXTPL = M::MAXTPL;
+    extern __shared__ __align__(16) float sh[];
     const int leaf = a.wleaf[blockIdx.x];
     const int64_t t_first = a.tbeg[leaf] + a.wt0[blockIdx.x];
     const int nt = (int)min((int64_t)64, a.tend[leaf] - t_first);
@@ -482,13 +533,13 @@ __global__ __launch_bounds__(64) void k_eval(EvalArgs a, SurfaceGeom g, PointSrc
         }
     }
     if constexpr (MAXTPL == 4) {
-        if (best == 4) return eval_item<4, NRHS, SL, DL, FIELD>(a, g, src, leaf, t_first, nt, sh, sh);
-        if (best == 3) return eval_item<3, NRHS, SL, DL, FIELD>(a, g, src, leaf, t_first, nt, sh, sh);
+        if (best == 4) return eval_item<4, NRHS, SL, DL, FIELD, MW, M::N>(a, g, src, leaf, t_first, nt, sh);
+        if (best == 3) return eval_item<3, NRHS, SL, DL, FIELD, MW, M::N>(a, g, src, leaf, t_first, nt, sh);
     }
     if (best >= 2)
-        eval_item<2, NRHS, SL, DL, FIELD>(a, g, src, leaf, t_first, nt, sh, sh);
+        eval_item<2, NRHS, SL, DL, FIELD, MW, M::N>(a, g, src, leaf, t_first, nt, sh);
     else
-        eval_item<1, NRHS, SL, DL, FIELD>(a, g, src, leaf, t_first, nt, sh, sh);
+        eval_item<1, NRHS, SL, DL, FIELD, MW, M::N>(a, g, src, leaf, t_first, nt, sh);
 }
 
 // ------------------------------------------------------------ all pairs
@@ -737,18 +788,26 @@ void points_to_surface(int nrhs, bool sl, bool dl, const int32_t *items, int nit
 void eval_leaves(int nrhs, bool sl, bool dl, const EvalArgs &a, const SurfaceGeom &g, const PointSrc &src,
                  hipStream_t s) {
     if (a.nwork <= 0) return;
-    dim3 gr(a.nwork), bl(64);
+    const int nw = a.waves;
+    FMM_REQUIRE(nw >= 1 && nw <= kEvalMaxWaves && (nw == 1 || a.pcum), "eval_leaves: waves per item");
     const bool field = a.field != nullptr;
+    auto go = [&](auto kern1, auto kern, int floats) {
+        hipLaunchKernelGGL((nw == 1 ? kern1 : kern), dim3(a.nwork), dim3(64 * nw), (size_t)nw * floats * sizeof(float), s,
+                           a, g, src);
+    };
+#define FMM_EVAL_GO(SL, DL, FIELD) \
+    FMM_NRHS_SWITCH(nrhs, go(k_eval<R, SL, DL, FIELD, false>, k_eval<R, SL, DL, FIELD, true>, EvalLds<R, SL, DL, FIELD>::N))
     if (field) {
         FMM_REQUIRE(sl && !dl, "field output is defined for the single layer only");
-        FMM_NRHS_SWITCH(nrhs, hipLaunchKernelGGL((k_eval<R, true, false, true>), gr, bl, 0, s, a, g, src));
+        FMM_EVAL_GO(true, false, true);
     } else if (sl && dl) {
-        FMM_NRHS_SWITCH(nrhs, hipLaunchKernelGGL((k_eval<R, true, true, false>), gr, bl, 0, s, a, g, src));
+        FMM_EVAL_GO(true, true, false);
     } else if (dl) {
-        FMM_NRHS_SWITCH(nrhs, hipLaunchKernelGGL((k_eval<R, false, true, false>), gr, bl, 0, s, a, g, src));
+        FMM_EVAL_GO(false, true, false);
     } else {
-        FMM_NRHS_SWITCH(nrhs, hipLaunchKernelGGL((k_eval<R, true, false, false>), gr, bl, 0, s, a, g, src));
+        FMM_EVAL_GO(true, false, false);
     }
+#undef FMM_EVAL_GO
     FMM_HIP(hipGetLastError());
 }
 

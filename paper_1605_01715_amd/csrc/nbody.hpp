@@ -38,6 +38,7 @@ void points_to_surface(int nrhs, bool sl, bool dl, const int32_t *items, int nit
 // prng[poff[leaf] .. poff[leaf+1]). Results go to pot[r * n_trg + perm[k]] and
 // field[(r * n_trg + perm[k]) * 3 + c] (user order), overwriting (accumulate =
 // 0) or added to what is there (accumulate = 1).
+constexpr int kEvalMaxWaves = 8;
 struct EvalArgs {
     const int32_t *wleaf = nullptr, *wt0 = nullptr;
     int nwork = 0;
@@ -56,6 +57,8 @@ struct EvalArgs {
     int accumulate = 0;
     int surf_mask = 3;  // surface kinds evaluated: bit 0 kind 0 (phi_d), bit 1 kind 1 (phi_u)
     int points = 1;     // 0: skip the point ranges (surfaces only)
+    int waves = 1;      // waves that share each work item's sources, 1..kEvalMaxWaves
+    const int32_t *pcum = nullptr;  // per range: the sources in its leaf's ranges before it (waves > 1)
 };
 void eval_leaves(int nrhs, bool sl, bool dl, const EvalArgs &a, const SurfaceGeom &g, const PointSrc &src,
                  hipStream_t s);

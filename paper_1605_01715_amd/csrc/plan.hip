@@ -229,6 +229,50 @@ void merge_ranges(std::vector<int32_t> &r, size_t from) {
     r.push_back(b);
 }
 
+// The waves that share each of the evaluation's work items, and the items'
+// order. Where leaves of different levels meet, a few items have many times
+// the mean number of sources (16,725 against 1,131 on eight spheres of 24,500
+// points): one wave each, they end long after the rest.
+//
+// Waves per item: the fewest with which the longest item ends within about a
+// third more than an even share of the work on each of the 1024 SIMDs, and
+// keeps two tiles of sources a wave. More waves end sooner but stage and
+// reduce more (4M cloud, longest 0.13 of a share: 4.17 ms with one, 4.22 with
+// two, 4.90 with four). Measured (kernel, one wave -> chosen): eight spheres,
+// 196,000 points, longest 5.5 shares: 1019 -> 200 us with 8; 39,200 points on
+// 40 spheres with the field, 3.5: 220 -> 134 us with 4; a body of 14,700
+// points, 5.3: 59 -> 25 us with 4; 5762 nodes of a surface under 80,640
+// sources, 4.0: 167 -> 61 us with 4.
+//
+// Where more than one is needed, the items of more than eight, four and two
+// times the mean cost also start first. Otherwise the items keep the leaves'
+// order, in which neighbours read the same sources (a 300,000-point cloud,
+// longest 1.0 of a share: apply 1907 us, and 1930 with the longest first).
+void order_eval_items(Plan &P, std::vector<int32_t> &wleaf, std::vector<int32_t> &wt0, const std::vector<float> &cost) {
+    const size_t n = wleaf.size();
+    P.eval_waves = 1;
+    double sum = 0.0, top = 0.0;
+    for (float c : cost) {
+        sum += c;
+        top = std::max(top, (double)c);
+    }
+    while (P.eval_waves < kEvalMaxWaves && top > std::max(1.35 * sum / 1024.0, 128.0) * P.eval_waves) P.eval_waves *= 2;
+    if (P.eval_waves == 1) return;
+    const double mean = sum / (double)n;
+    auto rank_of = [&](float c) { return c > 8 * mean ? 0 : c > 4 * mean ? 1 : c > 2 * mean ? 2 : 3; };
+    std::vector<int32_t> leaf2, t2;
+    leaf2.reserve(n);
+    t2.reserve(n);
+    for (int r = 0; r < 4; ++r)
+        for (size_t i = 0; i < n; ++i)
+            if (rank_of(cost[i]) == r) {
+                leaf2.push_back(wleaf[i]);
+                t2.push_back(wt0[i]);
+            }
+    wleaf.swap(leaf2);
+    wt0.swap(t2);
+}
+
 }  // namespace
 
 void plan_build_worklists(Plan &P, hipStream_t s) {
@@ -750,7 +794,8 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
     // check-to-equivalent maps and the leaf evaluation lists
     std::vector<int32_t> down_boxes;
     std::vector<uint8_t> up_needed(nb, 0);
-    std::vector<int32_t> wleaf, wt0, soff{0}, sbox, poff{0}, prng, pmid;
+    std::vector<int32_t> wleaf, wt0, soff{0}, sbox, poff{0}, prng, pmid, pcum;
+    std::vector<float> wcost;  // per work item, see below
     std::vector<int8_t> skind;
     // Which point ranges need the r < delta test: tight bounding boxes of the
     // target points of every target leaf and of the source points of every
@@ -868,15 +913,26 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         for (size_t e = 0; e < o.rf.size(); e += 2) npts += o.rf[e + 1] - o.rf[e];
         P.p2p_pairs += npts * ntrg(b);
         tested_pairs += ntest * ntrg(b);
+        int32_t run = 0;
+        for (const auto *r : {&o.rt, &o.rf})
+            for (size_t e = 0; e < r->size(); e += 2) {
+                pcum.push_back(run);
+                run += (*r)[e + 1] - (*r)[e];
+            }
         soff.push_back((int32_t)sbox.size());
         poff.push_back((int32_t)(prng.size() / 2));
         for (int64_t t0 = 0; t0 < ntrg(b); t0 += 64) {
             wleaf.push_back(b);
             wt0.push_back((int32_t)t0);
+            // a wave's time on the item: its sources times the lane-slots of
+            // its targets, plus about a tenth of a full item's for staging
+            wcost.push_back((float)(npts + (int64_t)o.wsurf.size() * ns) *
+                            ((float)std::min<int64_t>(64, ntrg(b) - t0) / 64.f + 0.1f));
         }
     }
     ll.clear();
     wl("evaluation lists");
+    order_eval_items(P, wleaf, wt0, wcost);
     // soff/poff are indexed by leaf id: expand to all boxes
     {
         std::vector<int32_t> so(nb + 1, 0), po(nb + 1, 0), pm(nb, 0);
@@ -908,6 +964,7 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
     P.skind = upload(skind, s);
     prng.insert(prng.end(), 8, 0);  // the evaluation reads bounds up to 8 entries ahead
     P.prng = upload(prng, s);
+    P.pcum = upload(pcum, s);
     {
         GemmJob &j = P.c2e_down;
         std::vector<int32_t> cols = tile_columns(down_boxes, nrhs, ncol64, j.ntile);
@@ -1126,6 +1183,8 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
     e.poff = P.poff.p;
     e.prng = P.prng.p;
     e.pmid = P.pmid.p;
+    e.pcum = P.pcum.p;
+    e.waves = P.eval_waves;
     e.tbeg = t.tbeg.p;
     e.tend = t.tend.p;
     if (t.tsm) {
@@ -1242,6 +1301,7 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
         ef.surf_mask = 1;  // L2P: the leaf's own downward surface, added to the near field
         ef.points = 0;
         ef.accumulate = 1;
+        ef.waves = 1;
         eval_leaves(nrhs, sl, dl, ef, g, src, s);
     }
     mark(ST_COUNT);
