@@ -7,18 +7,24 @@
 // of point-generated check potentials onto the compressed basis and the
 // check-to-equivalent expansions. They are cheap next to M2L and they feed
 // every M2L, so they run in float64 (v_mfma_f64_16x16x4_f64) on float32 data.
-// The kernel is target-stationary: a workgroup owns 64 rows of a tile of 32
-// output vectors, keeps their accumulator in registers across all terms and
-// writes each output once.
+// The kernel is target-stationary: 1, 2, 4 or 8 waves own 16 rows of a tile of
+// 32 output vectors, keep their accumulators in registers across all terms
+// and write each output once.
 //
-// Layout (4 waves of 64 lanes): the workgroup (tile, g) computes row blocks
-// 4g .. 4g+3 of 16 rows, wave w row block 4g + w against both 16-column
-// blocks. Splitting the rows over workgroups keeps the chain of float64
-// MFMAs of one tile short: most tree levels have fewer tiles than the chip
-// has CUs, so a level costs about one tile's latency (measured 3x faster
-// than one workgroup per tile). Matrices are stored in the fragment order of
-// the instruction; the source vectors of the tile are staged in LDS and
-// shared by the four waves.
+// Bound: at the sizes of one tree level, latency. Most levels have fewer
+// tiles than the chip has CUs, and a parent's eight child terms are one chain
+// of 8 K / 16 steps of eight float64 MFMAs (64 cycles each). So the (term, k)
+// steps of an output block are shared by `split` waves, whose partial sums are
+// added in LDS in a fixed order; with eight, an M2M wave runs one child.
+// Matrices are stored in fragment order and both operands go straight from
+// global memory to registers (lane group g of a fragment holds k = 4 g + s for
+// MFMA s, the same on both sides, so that a lane's four k of a vector are one
+// 16-byte load), the next step's loads under the current step's MFMAs: no
+// barrier before the final sum. Against staging the vectors in LDS for four
+// row blocks and running the terms in sequence: M2M of 200 to 600 boxes at K =
+// 224 87-104 -> 13-23 us, L2L of the same 15-19 -> 8 us, projections of 4274
+// boxes 28 -> 22 us; the surface form's apply on eight spheres (196,000 points)
+// 1092 -> 754 us and on a 4M cloud (order 8) 9.07 -> 8.80 ms.
 #include "gemm.hpp"
 
 #include <algorithm>
@@ -29,107 +35,100 @@ namespace {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kThreads = 256;
-
-// The tile's source vectors of one term are staged in LDS 128 k at a time
-// (float32, [k][column], 18 KB, so up to eight workgroups share a CU and
-// cover each other's staging and barriers), and the matrix fragments of the
-// next 16-k chunk are loaded while the current chunk's MFMAs run.
 constexpr int kMaxK = 512;
-constexpr int kKChunk = 128;          // k rows staged at a time
-constexpr int kBStr = kGemmCols + 4;  // floats per k row in LDS
+constexpr int kGemmWaves = 8;  // per workgroup: 8 / split row blocks of one tile
 
-template <int MAXRB>
-__global__ __launch_bounds__(kThreads) void k_gemm_f64(GemmLaunch a) {
-    constexpr int NCOL = kGemmCols;
-    extern __shared__ float Bs[];  // [kKChunk][kBStr]
-    __shared__ int32_t cols[NCOL], srcs[NCOL];
-    const int t = threadIdx.x, lane = t & 63;
-    const int w = __builtin_amdgcn_readfirstlane(t >> 6) + 4 * MAXRB * (int)blockIdx.y;  // first row block
+// D: steps whose loads are in flight
+template <int D>
+__global__ __launch_bounds__(64 * kGemmWaves) void k_gemm_f64(GemmLaunch a, int split) {
+    __shared__ double red[kGemmWaves][8][64];  // partial sums: [wave][column block, element][lane]
+    const int lane = threadIdx.x & 63, c16 = lane & 15, g = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int part = w % split;
+    const int nrb = a.m_pad / 16, nkc = a.k_pad / 16;
+    const int rb = (int)blockIdx.y * (kGemmWaves / split) + w / split;  // wave-uniform
+    const bool live = rb < nrb;
     const int64_t tile = blockIdx.x;
-    const int nrb = a.m_pad / 16, K = a.k_pad, nkc = K / 16;
-    if (t < NCOL) cols[t] = a.tile_cols[tile * NCOL + t];
-    f64x4 acc[MAXRB][2];
-#pragma unroll
-    for (int i = 0; i < MAXRB; ++i)
-        for (int c = 0; c < 2; ++c) acc[i][c] = f64x4{0.0, 0.0, 0.0, 0.0};
-    for (int term = 0; term < a.nterm; ++term) {
-        __syncthreads();
-        int mysrc = -1;
-        if (t < NCOL) {
-            mysrc = a.term_src[(tile * a.nterm + term) * NCOL + t];
-            srcs[t] = mysrc;
+    f64x4 acc[2];
+    acc[0] = acc[1] = f64x4{0.0, 0.0, 0.0, 0.0};
+    if (live) {
+        // this wave's steps [s0, s1) of the tile's nterm * nkc, term by term
+        const int total = a.nterm * nkc;
+        const int s0 = total * part / split, s1 = total * (part + 1) / split;
+        const int32_t *ts = a.term_src + (size_t)tile * a.nterm * kGemmCols + c16;
+        struct Frag {
+            double a[4];
+            float4 b[2];
+        };
+        Frag f[D];
+        int term = s0 / nkc;
+        int32_t n0 = 0, n1 = 0;  // the next term's sources of the lane's two columns
+        if (s0 < s1) {
+            n0 = ts[term * kGemmCols];
+            n1 = ts[term * kGemmCols + 16];
         }
-        if (!__syncthreads_or(mysrc >= 0)) continue;
-        const int mat = a.term_mat ? a.term_mat[tile * a.nterm + term] : term;
-        const double *M = a.mats + (size_t)mat * a.mat_elems;
-        // matrix fragments: av[i][s] for row block w + 4 i, chunk kc
-        double av0[MAXRB][4], av1[MAXRB][4];
-        auto load_av = [&](double (&av)[MAXRB][4], int kc) {
-#pragma unroll
-            for (int i = 0; i < MAXRB; ++i) {
-                const int rb = min(w + 4 * i, nrb - 1);  // clamped rows are loaded, never used
-                const double *ap = M + (((size_t)rb * nkc + kc) * 64 + lane) * 4;
-                for (int s = 0; s < 4; ++s) av[i][s] = ap[s];
+        for (int at = s0; at < s1; ++term) {
+            const int k0 = at - term * nkc, k1 = min(nkc, s1 - term * nkc);
+            at += k1 - k0;
+            const int32_t v0 = n0, v1 = n1;
+            if (at < s1) {
+                n0 = ts[(term + 1) * kGemmCols];
+                n1 = ts[(term + 1) * kGemmCols + 16];
             }
-        };
-        // chunk kc against the staged rows lk * 16 .. lk * 16 + 15 of the LDS slice
-        auto mma = [&](const double (&av)[MAXRB][4], int lk) {
-            double bf[4][2];
-            for (int s = 0; s < 4; ++s)
-                for (int cb = 0; cb < 2; ++cb)
-                    bf[s][cb] = (double)Bs[(lk * 16 + 4 * s + (lane >> 4)) * kBStr + cb * 16 + (lane & 15)];
+            if (__ballot(v0 >= 0 || v1 >= 0) == 0) continue;  // no column has a source
+            const int mat = a.term_mat ? a.term_mat[(size_t)tile * a.nterm + term] : term;
+            const double *ap = a.mats + (size_t)mat * a.mat_elems + ((size_t)rb * nkc * 64 + lane) * 4;
+            const float4 *b0 = (const float4 *)(a.in + (size_t)max(v0, 0) * a.k_pad) + g;
+            const float4 *b1 = (const float4 *)(a.in + (size_t)max(v1, 0) * a.k_pad) + g;
+            auto load = [&](Frag &x, int kc) {
+                kc = min(kc, k1 - 1);  // past the term's end its last step again: no branch around the loads
+                const double *q = ap + (size_t)kc * 256;
 #pragma unroll
-            for (int i = 0; i < MAXRB; ++i) {
-                if (w + 4 * i >= nrb) continue;
+                for (int s = 0; s < 4; ++s) x.a[s] = q[s];
+                x.b[0] = b0[4 * kc];
+                x.b[1] = b1[4 * kc];
+            };
+            auto mma = [&](const Frag &x) {
+#pragma unroll
                 for (int s = 0; s < 4; ++s)
-                    for (int cb = 0; cb < 2; ++cb)
-                        acc[i][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i][s], bf[s][cb], acc[i][cb], 0, 0, 0);
-            }
-        };
-        for (int k0 = 0; k0 < K; k0 += kKChunk) {
-            const int kn = min(kKChunk, K - k0);  // a multiple of 16
-            if (k0 > 0) __syncthreads();         // every wave is done with the previous slice
-            // stage k0 .. k0 + kn of the 32 source vectors, transposed
-            const int kq = kn / 4;
-            for (int idx = t; idx < NCOL * kq; idx += kThreads) {
-                const int col = idx / kq, k4 = (idx % kq) * 4;
-                const int sidx = srcs[col];
-                float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (sidx >= 0) x = *(const float4 *)(a.in + (size_t)sidx * K + k0 + k4);
-                Bs[(k4 + 0) * kBStr + col] = x.x;
-                Bs[(k4 + 1) * kBStr + col] = x.y;
-                Bs[(k4 + 2) * kBStr + col] = x.z;
-                Bs[(k4 + 3) * kBStr + col] = x.w;
-            }
-            __syncthreads();
-            const int c0 = k0 / 16, c1 = (k0 + kn) / 16;
-            load_av(av0, c0);
-            for (int kc = c0; kc < c1; kc += 2) {
-                if (kc + 1 < c1) load_av(av1, kc + 1);
-                mma(av0, kc - c0);
-                if (kc + 1 < c1) {
-                    if (kc + 2 < c1) load_av(av0, kc + 2);
-                    mma(av1, kc + 1 - c0);
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb) {
+                        const float4 v = x.b[cb];
+                        const float e = s == 0 ? v.x : s == 1 ? v.y : s == 2 ? v.z : v.w;
+                        const double bv = (double)((cb ? v1 : v0) < 0 ? 0.f : e);
+                        acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(x.a[s], bv, acc[cb], 0, 0, 0);
+                    }
+            };
+#pragma unroll
+            for (int d = 0; d < D - 1; ++d) load(f[d], k0 + d);
+            for (int kc = k0; kc < k1; kc += D) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    load(f[(d + D - 1) % D], kc + d + D - 1);
+                    if (kc + d < k1) mma(f[d]);
                 }
             }
         }
     }
+    const int j0 = part * (8 / split);  // of the block's 8 elements per lane, this wave writes 8 / split
+    if (split > 1) {
 #pragma unroll
-    for (int i = 0; i < MAXRB; ++i) {
-        const int rb = w + 4 * i;
-        if (rb >= nrb) continue;
-        for (int cb = 0; cb < 2; ++cb) {
-            const int o = cols[cb * 16 + (lane & 15)];
-            if (o < 0) continue;
-            const double sc = a.col_scale ? a.col_scale[o] : 1.0;
-            // f64 16x16 accumulator: element v of lane l is row l/16 + 4 v
-            float *op = a.out + (size_t)o * a.m_pad + rb * 16 + (lane >> 4);
-            for (int v = 0; v < 4; ++v) {
-                float r = (float)(acc[i][cb][v] * sc);
-                op[4 * v] = a.accumulate ? op[4 * v] + r : r;
-            }
-        }
+        for (int j = 0; j < 8; ++j) red[w][j][lane] = acc[j >> 2][j & 3];
+        __syncthreads();
+    }
+    if (!live) return;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        if (j < j0 || j >= j0 + 8 / split) continue;
+        const int o = a.tile_cols[tile * kGemmCols + 16 * (j >> 2) + c16];
+        if (o < 0) continue;
+        double sum = split > 1 ? red[w - part][j][lane] : acc[j >> 2][j & 3];
+        for (int p = 1; p < split; ++p) sum += red[w - part + p][j][lane];
+        const double sc = a.col_scale ? a.col_scale[o] : 1.0;
+        // f64 16x16 accumulator: element v of lane l is row l / 16 + 4 v
+        float *op = a.out + (size_t)o * a.m_pad + rb * 16 + g + 4 * (j & 3);
+        const float r = (float)(sum * sc);
+        *op = a.accumulate ? *op + r : r;
     }
 }
 
@@ -143,7 +142,7 @@ __global__ void k_frag_f64(const double *M, int rows, int cols, int m_pad, int k
     r /= 64;
     int kc = (int)(r % nkc);
     int rb = (int)(r / nkc);
-    int row = rb * 16 + (lane & 15), k = kc * 16 + 4 * s + (lane >> 4);
+    int row = rb * 16 + (lane & 15), k = kc * 16 + 4 * (lane >> 4) + s;
     out[idx] = (row < rows && k < cols) ? M[(int64_t)row * cols + k] : 0.0;
 }
 
@@ -319,10 +318,20 @@ void box_gemm_f64(const GemmLaunch &a, hipStream_t s) {
     if (a.ntile <= 0 || a.nterm <= 0) return;
     FMM_REQUIRE(a.m_pad % 16 == 0 && a.k_pad % 16 == 0 && a.m_pad <= 512 && a.k_pad <= kMaxK,
                 "box_gemm: unsupported size");
-    dim3 g((unsigned)a.ntile, (unsigned)((a.m_pad / 16 + 3) / 4)), b(kThreads);  // one row block per wave
-    const size_t sh = (size_t)std::min(a.k_pad, kKChunk) * kBStr * sizeof(float);
-    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, g, b, sh, s, a); };
-    go(k_gemm_f64<1>);
+    // waves per output block: enough for two on each of the 1024 SIMDs
+    const int nrb = a.m_pad / 16;
+    int split = 1;
+    while (split < kGemmWaves && (int64_t)a.ntile * nrb * split < 2048) split *= 2;
+    const int per = kGemmWaves / split;  // row blocks per workgroup
+    const dim3 g((unsigned)a.ntile, (unsigned)((nrb + per - 1) / per)), b(64 * kGemmWaves);
+    // A child term of 12 steps or more (K >= 192) hides more of its loads'
+    // latency with four steps in flight (K = 224, few tiles: 21 -> 14 us);
+    // shorter runs only load what they do not use (K = 224 in two steps a
+    // wave: 7.7 -> 9.1 us)
+    if (a.nterm > 1 && a.k_pad >= 192)
+        hipLaunchKernelGGL(k_gemm_f64<4>, g, b, 0, s, a, split);
+    else
+        hipLaunchKernelGGL(k_gemm_f64<2>, g, b, 0, s, a, split);
     FMM_HIP(hipGetLastError());
 }
 
