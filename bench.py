@@ -200,11 +200,7 @@ def roofline(res, precision, n, cfg):
                                  "gather, which run beside the leaf evaluation on the plan's second stream")
         others["P2L"]["note"] = "runs on the plan's second stream beside P2M and M2M"
     else:
-        # the surface form's P2L is the first work on the caller's stream after the fork: its stage time is
-        # mostly queueing behind the leaf evaluation's workgroups, not a kernel time
-        others["P2L"].update({"achieved_tflops": None, "frac": None,
-                              "note": "stage time includes queueing behind the leaf evaluation on the second "
-                                      "stream; the kernel time is in the rocprofv3 trace"})
+        others["P2L"]["note"] = "runs, with its projection, on the plan's second stream beside P2M and M2M"
     return out, others
 
 

@@ -442,10 +442,11 @@ int fmm_export_stage(fmm_plan plan, int which, float *host_out);
  * timing on (fmm_set_timing) since the previous call, which this call waits
  * for; when there were none since, the previous means again; -1 when no apply
  * was ever timed. Order: P2M, M2M, P2L, M2L, L2L, C2E, EVAL.
- * Both forms run the leaf evaluation's near field on a second stream beside
- * M2L (its time is taken there). CHEBYSHEV plans also run P2L there, C2E is
- * their L2P, and their M2L stage times the translation kernel, the reduction
- * and the gather, while the split of its input (split-BF16) is in no stage.
+ * Both forms run P2L (SURFACE: with its projection), beside P2M and M2M, and
+ * the leaf evaluation's near field, beside M2L, on a second stream (their
+ * times are taken there). CHEBYSHEV plans' C2E is their L2P, and their M2L
+ * stage times the translation kernel, the reduction and the gather, while the
+ * split of its input (split-BF16) is in no stage.
  * SURFACE plans expand the upward densities in the M2M stage, and their EVAL
  * is the near field (second stream) plus the L2P pass after the join. */
 int fmm_stage_times(fmm_plan plan, double *ms /* [7] */);

@@ -1066,17 +1066,17 @@ static void collect_slot(Plan &P, Plan::TimeSlot &ts) {
         ms_k[k] = ms;
     }
     float ms = 0.f;
+    // P2L ran on the side stream
+    FMM_HIP(hipEventElapsedTime(&ms, ts.side[0], ts.side[1]));
+    ms_k[ST_P2L] = ms;
+    FMM_HIP(hipEventElapsedTime(&ms, ts.side[2], ts.side[3]));
     if (P.cheb) {
-        // L2L ends before the join; P2L and the evaluation ran on the side stream
+        // so did the evaluation; L2L ends before the join
+        ms_k[ST_EVAL] = ms;
         FMM_HIP(hipEventElapsedTime(&ms, ts.ev[ST_L2L], ts.l2l_end));
         ms_k[ST_L2L] = ms;
-        FMM_HIP(hipEventElapsedTime(&ms, ts.side[0], ts.side[1]));
-        ms_k[ST_P2L] = ms;
-        FMM_HIP(hipEventElapsedTime(&ms, ts.side[2], ts.side[3]));
-        ms_k[ST_EVAL] = ms;
     } else {
         // the near field ran on the side stream; EVAL is it plus the L2P pass
-        FMM_HIP(hipEventElapsedTime(&ms, ts.side[2], ts.side[3]));
         ms_k[ST_EVAL] += ms;
     }
     for (int k = 0; k < ST_COUNT; ++k) P.stage_sum[k] += ms_k[k];
@@ -1207,6 +1207,21 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
     e.delta2 = std::max(P.opt.cutoff * P.opt.cutoff, std::numeric_limits<float>::min());
     e.pot = pot;
     e.field = field;
+    // P2L needs only the points: it runs first on the side stream, beside P2M
+    // and M2M (without X-list work the streams are not tied together here)
+    const bool p2l = P.n_p2l > 0 || ts;
+    auto side_p2l = [&](auto &&work) {
+        if (!p2l) return;
+        FMM_HIP(hipEventRecord(P.fork0, s));
+        FMM_HIP(hipStreamWaitEvent(P.side, P.fork0, 0));
+        if (ts) FMM_HIP(hipEventRecord(ts->side[0], P.side));
+        work();
+        if (ts) FMM_HIP(hipEventRecord(ts->side[1], P.side));
+        FMM_HIP(hipEventRecord(P.p2l_done, P.side));
+    };
+    auto wait_p2l = [&] {
+        if (p2l) FMM_HIP(hipStreamWaitEvent(s, P.p2l_done, 0));
+    };
     if (P.cheb) {
         // Chebyshev form (Sec. III.A.1 Eq. p2m): node weights W (phi_u) up the
         // tree, node values L (phi_d) down; M2L in the shared compressed basis.
@@ -1217,13 +1232,10 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
         // other box the downward pass reads (all boxes with targets from
         // level 2) and adds to P2L's, and the rest stay zero from the setup.
         // side stream, first: P2L at the nodes, beside P2M and M2M
-        FMM_HIP(hipEventRecord(P.fork0, s));
-        FMM_HIP(hipStreamWaitEvent(P.side, P.fork0, 0));
-        if (ts) FMM_HIP(hipEventRecord(ts->side[0], P.side));
-        points_to_surface(nrhs, sl, dl, P.p2l_items.p, P.n_p2l, P.p2l_roff.p, P.p2l_rng.p, 1.0, g, src, P.phi_d.p,
-                          false, P.side);
-        if (ts) FMM_HIP(hipEventRecord(ts->side[1], P.side));
-        FMM_HIP(hipEventRecord(P.p2l_done, P.side));
+        side_p2l([&] {
+            points_to_surface(nrhs, sl, dl, P.p2l_items.p, P.n_p2l, P.p2l_roff.p, P.p2l_rng.p, 1.0, g, src, P.phi_d.p,
+                              false, P.side);
+        });
         mark(ST_P2M);
         points_to_nodes(nrhs, sl, dl, op.p, op.cheb_coef.p, P.p2m_items.p, P.n_p2m, P.p2m_roff.p, P.p2m_rng.p, g, src,
                         P.phi_u.p, s);
@@ -1252,7 +1264,7 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
         mark(ST_L2L);
         // the downward pass starts by expanding the M2L result onto the nodes,
         // adding to the P2L values
-        FMM_HIP(hipStreamWaitEvent(s, P.p2l_done, 0));
+        wait_p2l();
         dense_gemm_f32(np, rp, P.cheb_expand.ntile, P.cheb_expand.cols.p, op.cd_f32.p, P.dt.p, P.phi_d.p,
                        P.col_iscale.p, 0, s, P.expand_add.p);
         for (auto &j : P.cheb_l2l)
@@ -1267,8 +1279,18 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
     } else {
         // Surface form: the near field and M2P (the leaf evaluation without
         // L2P) need only the upward equivalent densities, so after the upward
-        // pass they run on the side stream beside P2L, M2L, L2L and the
-        // downward expansion; L2P adds to the outputs after the join.
+        // pass they run on the side stream beside M2L, L2L and the downward
+        // expansion; L2P adds to the outputs after the join. P2L and its
+        // projection onto the M2L output run there first: queued on the
+        // caller's stream after the fork they waited for wave slots behind the
+        // evaluation (78 and 77 us for 446 boxes of a 300,000-point cloud,
+        // apply 1633 -> 1593 us without that). The check potentials use the
+        // rows of phi_d, which the downward expansion writes only after M2L.
+        side_p2l([&] {
+            points_to_surface(nrhs, sl, dl, P.p2l_items.p, P.n_p2l, P.p2l_roff.p, P.p2l_rng.p, kRadIn, g, src,
+                              P.phi_d.p, false, P.side);
+            run_gemm(P.p2l_proj, op.pv_f64.p, rp, np, P.phi_d.p, P.dt.p, nullptr, true, P.side);
+        });
         mark(ST_P2M);
         points_to_surface(nrhs, sl, dl, P.p2m_items.p, P.n_p2m, P.p2m_roff.p, P.p2m_rng.p, kRadOut, g, src, P.chk.p,
                           false, s);
@@ -1284,10 +1306,8 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
         eval_leaves(nrhs, sl, dl, en, g, src, P.side);
         if (ts) FMM_HIP(hipEventRecord(ts->side[3], P.side));
         FMM_HIP(hipEventRecord(P.join, P.side));
-        mark(ST_P2L);
-        points_to_surface(nrhs, sl, dl, P.p2l_items.p, P.n_p2l, P.p2l_roff.p, P.p2l_rng.p, kRadIn, g, src, P.chk.p,
-                          false, s);
-        run_gemm(P.p2l_proj, op.pv_f64.p, rp, np, P.chk.p, P.dt.p, nullptr, true, s);
+        mark(ST_P2L);  // (P2L runs on the side stream; timed there)
+        wait_p2l();
         mark(ST_M2L);
         split_m2l_input();
         run_m2l();

@@ -100,9 +100,9 @@ struct Plan {
         std::array<const void *, 4> key{};
     } graph;
 
-    // Chebyshev form: P2L (needs only the points) and the leaf evaluation
-    // (near field and M2P, needs only the node weights) run on a plan-owned
-    // side stream, beside P2M/M2M and M2L/L2L on the caller's stream
+    // P2L (needs only the points) and the leaf evaluation (near field and M2P,
+    // needs only the upward pass) run on a plan-owned side stream, beside
+    // P2M/M2M and M2L/L2L on the caller's stream
     hipStream_t side = nullptr;
     hipEvent_t fork0 = nullptr, p2l_done = nullptr, fork = nullptr, join = nullptr;
 
