@@ -440,8 +440,8 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         // partners (points on surfaces), a tile runs every direction for
         // only a fraction of its columns (fill 0.2-0.3 on the sphere
         // workloads). The (direction, target) pairs of tiles with fill below
-        // kPairFill are regrouped by octant and direction into tiles of one
-        // direction whose columns are pairs, all live; each writes its
+        // kPairFill are regrouped by direction into tiles of one direction
+        // whose columns are pairs, all live; each writes its
         // products to a partial-sum slot, and a gather adds each target's
         // partials in direction order. Costs: a tile does 6 steps per
         // direction; a pair tile 6 steps plus writing and reading back its
@@ -453,8 +453,8 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         constexpr double kPairFill = 0.45;
         std::vector<uint8_t> pair_tile(ntile, 0);
         {
-            // the columns of the sparse tiles, per octant
-            std::vector<std::vector<int32_t>> sparse(8);
+            // the columns of the sparse tiles
+            std::vector<int32_t> sparse;
             std::vector<uint8_t> keep(ntile, 1);
             bool moved = false;
             for (int tl = 0; tl < ntile; ++tl) {
@@ -466,7 +466,7 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
                 moved = true;
                 for (int c = 0; c < nc; ++c) {
                     const int32_t v = cols[(size_t)tl * nc + c];
-                    if (v >= 0) sparse[tile_oct[tl]].push_back(v);
+                    if (v >= 0) sparse.push_back(v);
                 }
             }
             if (moved) {
@@ -482,46 +482,62 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
                     oct2.push_back(tile_oct[tl]);
                     pair2.push_back(0);
                 }
-                // per octant (in parallel), the (direction, target) pairs ordered
-                // by direction, then target: a counting sort over the directions
-                // of the targets taken in increasing order
-                std::vector<std::vector<int32_t>> pdir(8), pcols(8);
+                // the (direction, target) pairs ordered by direction, then target:
+                // a counting sort over the directions of the targets taken in
+                // increasing order, in parallel over chunks of the targets
+                std::sort(sparse.begin(), sparse.end());
+                const int nchunk = (int)std::max<size_t>(1, std::min<size_t>(64, sparse.size() / 64));
+                auto chunk_at = [&](int k) { return sparse.size() * (size_t)k / (size_t)nchunk; };
+                std::vector<int64_t> pos((size_t)nchunk * kNumDirs, 0), start(kNumDirs + 1, 0);
+                auto each_dir = [&](int32_t v, auto &&f) {
+                    const uint64_t *m = mask_of(v / nrhs);
+                    for (int w = 0; w < kMaskWords; ++w)
+                        for (uint64_t bits = m[w]; bits; bits &= bits - 1) f(w * 64 + 63 - __builtin_ctzll(bits));
+                };
 #pragma omp parallel for schedule(dynamic, 1)
-                for (int o = 0; o < 8; ++o) {
-                    std::vector<int32_t> &sv = sparse[o];
-                    std::sort(sv.begin(), sv.end());
-                    std::vector<int64_t> start(kNumDirs + 1, 0);
-                    for (int32_t v : sv) {
-                        const uint64_t *m = mask_of(v / nrhs);
-                        for (int w = 0; w < kMaskWords; ++w)
-                            for (uint64_t bits = m[w]; bits; bits &= bits - 1)
-                                ++start[w * 64 + 63 - __builtin_ctzll(bits) + 1];
+                for (int k = 0; k < nchunk; ++k)
+                    for (size_t i = chunk_at(k); i < chunk_at(k + 1); ++i)
+                        each_dir(sparse[i], [&](int d) { ++pos[(size_t)k * kNumDirs + d]; });
+                for (int d = 0; d < kNumDirs; ++d) {
+                    int64_t run = start[d];
+                    for (int k = 0; k < nchunk; ++k) {
+                        const int64_t n = pos[(size_t)k * kNumDirs + d];
+                        pos[(size_t)k * kNumDirs + d] = run;
+                        run += n;
                     }
-                    for (int d = 0; d < kNumDirs; ++d) start[d + 1] += start[d];
-                    std::vector<int32_t> by_dir(start[kNumDirs]);
-                    std::vector<int64_t> pos(start.begin(), start.end() - 1);
-                    for (int32_t v : sv) {
-                        const uint64_t *m = mask_of(v / nrhs);
-                        for (int w = 0; w < kMaskWords; ++w)
-                            for (uint64_t bits = m[w]; bits; bits &= bits - 1)
-                                by_dir[pos[w * 64 + 63 - __builtin_ctzll(bits)]++] = v;
-                    }
-                    for (int d = 0; d < kNumDirs; ++d)
-                        for (int64_t i = start[d]; i < start[d + 1]; i += nc) {
-                            const int64_t j = std::min(start[d + 1], i + nc);
-                            pdir[o].push_back(d);
-                            for (int64_t q = i; q < i + nc; ++q) pcols[o].push_back(q < j ? by_dir[q] : -1);
-                        }
+                    start[d + 1] = run;
                 }
-                for (int o = 0; o < 8; ++o) {
-                    for (int32_t d : pdir[o]) {
+                std::vector<int32_t> by_dir(start[kNumDirs]);
+#pragma omp parallel for schedule(dynamic, 1)
+                for (int k = 0; k < nchunk; ++k)
+                    for (size_t i = chunk_at(k); i < chunk_at(k + 1); ++i)
+                        each_dir(sparse[i], [&](int d) { by_dir[pos[(size_t)k * kNumDirs + d]++] = sparse[i]; });
+                // Tiles of nc pairs of one direction, in direction order. The
+                // matrix depends on the direction only, so a tile takes the
+                // pairs of all octants (per octant, small plans had 1512 tiles
+                // of a few columns each: 14% of them used on 39,200 points on
+                // 40 spheres, 6% on a body of 14,700). XCD x gets a contiguous
+                // run of the tiles that brings its direction count, with that
+                // of its octant's own tiles, up to an even share.
+                int64_t npair = 0, xload[8] = {0, 0, 0, 0, 0, 0, 0, 0}, all = 0;
+                for (int d = 0; d < kNumDirs; ++d) npair += (start[d + 1] - start[d] + nc - 1) / nc;
+                for (size_t tl = 0; tl < oct2.size(); ++tl) xload[oct2[tl]] += toff2[tl + 1] - toff2[tl];
+                for (int x = 0; x < 8; ++x) all += xload[x];
+                all += npair;
+                cols2.reserve(cols2.size() + (size_t)npair * nc);
+                int x = 0;
+                for (int d = 0; d < kNumDirs; ++d)
+                    for (int64_t i = start[d]; i < start[d + 1]; i += nc) {
+                        while (x < 7 && xload[x] * 8 >= all) ++x;
+                        ++xload[x];
+                        const int64_t j = std::min(start[d + 1], i + nc);
                         tdir2.push_back(d);
                         toff2.push_back((int64_t)tdir2.size());
-                        oct2.push_back(o);
+                        oct2.push_back(x);
                         pair2.push_back(1);
+                        cols2.insert(cols2.end(), by_dir.begin() + i, by_dir.begin() + j);
+                        cols2.resize(cols2.size() + (size_t)(i + nc - j), -1);
                     }
-                    cols2.insert(cols2.end(), pcols[o].begin(), pcols[o].end());
-                }
                 toff.swap(toff2);
                 tdir.swap(tdir2);
                 cols.swap(cols2);
@@ -665,9 +681,9 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
                 P.m2l_red_k = upload(red_k, s);
             }
             // pair tiles: per target vector, its partial rows in direction
-            // order. A target's pair tiles were made from its octant's pairs
-            // in increasing direction, so they were met in that order above,
-            // and a stable counting sort by target keeps it.
+            // order. The pair tiles were made in increasing direction, so they
+            // were met in that order above, and a stable counting sort by
+            // target keeps it.
             std::vector<int32_t> gt, goff{0}, gidx(gather.size());
             {
                 const int64_t nvec = nb * nrhs;
