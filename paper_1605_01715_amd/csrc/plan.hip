@@ -111,17 +111,17 @@ struct Lap {
 
 // Per box b, bit 63 - d % 64 of out[b * kMaskWords + d / 64] is set when the
 // V partner in direction d exists and holds sources.
-__global__ void k_dir_masks(const int32_t *vdense, int64_t nb, const int64_t *sbeg, const int64_t *send,
-                            uint64_t *out) {
-    const int64_t b = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+// One wave per box, its lanes over the directions.
+__global__ __launch_bounds__(kBlock) void k_dir_masks(const int32_t *vdense, int64_t nb, const int64_t *sbeg,
+                                                      const int64_t *send, uint64_t *out) {
+    const int64_t b = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
     if (b >= nb) return;
+    const int lane = threadIdx.x & 63;
     for (int w = 0; w < kMaskWords; ++w) {
-        uint64_t m = 0;
-        for (int i = 0; i < 64 && w * 64 + i < kNumDirs; ++i) {
-            const int32_t a = vdense[b * kNumDirs + w * 64 + i];
-            if (a >= 0 && send[a] > sbeg[a]) m |= 1ull << (63 - i);
-        }
-        out[b * kMaskWords + w] = m;
+        const int d = w * 64 + lane;
+        const int32_t a = d < kNumDirs ? vdense[b * kNumDirs + d] : -1;
+        const uint64_t m = __ballot(a >= 0 && send[max(a, 0)] > sbeg[max(a, 0)]);
+        if (lane == 0) out[b * kMaskWords + w] = __brevll(m);
     }
 }
 
@@ -360,7 +360,7 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         std::vector<uint64_t> mask((size_t)nb * kMaskWords);
         {
             DBuf<uint64_t> dm(mask.size());
-            hipLaunchKernelGGL(k_dir_masks, dim3(grid_for(nb, kBlock)), dim3(kBlock), 0, s, t.vdense.p, nb,
+            hipLaunchKernelGGL(k_dir_masks, dim3(grid_for(nb, kBlock / 64)), dim3(kBlock), 0, s, t.vdense.p, nb,
                                t.sbeg.p, t.send.p, dm.p);
             FMM_HIP(hipGetLastError());
             d2h(mask.data(), dm.p, mask.size(), s);
