@@ -34,6 +34,9 @@
  *     ABI. On failure, fmm_last_error() returns a message describing it
  *     (thread-local, valid until the next call on the same thread).
  *   - Point arrays are float32, array-of-structures [n][3] (x, y, z).
+ *   - Device memory of destroyed plans and finished solves is kept for the
+ *     next ones, up to 512 MB a process; it is freed when the next eight do not
+ *     use it, or when an allocation of the library fails.
  *
  * Environment variables read by the library:
  *   FMM_LOG            set (and not "0"): diagnostics on stderr
@@ -202,7 +205,7 @@ typedef struct {
  * Gram-Schmidt twice) and residual norms are float64 on the device; one
  * fmm_apply and one device-to-host copy of the step's coefficients per
  * iteration. restart is 1..500; the Krylov basis takes (restart + 1) n
- * float64 of device memory, allocated per call.
+ * float64 of device memory, taken per call.
  *   b        device double [n]    right-hand side
  *   x        device double [n]    in: initial guess, out: solution (best iterate)
  *   iters    host int             iterations done

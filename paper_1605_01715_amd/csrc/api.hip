@@ -172,7 +172,10 @@ void finish_plan(fmm::Plan &P, const fmm_options *opt, const float *trg_nrm, hip
     };
     for (int k = 0; k < 3; ++k) P.setup_phase_ms[k] += P.t.phase_ms[k];
     double eps = opt->pinv_eps > 0 ? opt->pinv_eps : default_pinv_eps(opt->basis, opt->order);
-    P.ops = get_operators(opt->basis, opt->order, eps, s);
+    {
+        ArenaScope shared(nullptr, nullptr);  // the operators outlive the plan
+        P.ops = get_operators(opt->basis, opt->order, eps, s);
+    }
     phase_end(3);
     P.cheb = opt->basis == FMM_BASIS_CHEBYSHEV;
     P.ns = P.ops->ns;
@@ -182,7 +185,7 @@ void finish_plan(fmm::Plan &P, const fmm_options *opt, const float *trg_nrm, hip
     const size_t nvec = (size_t)P.t.nb * P.nrhs;
     P.ut.alloc(nvec * P.r_pad);
     P.dt.alloc(nvec * P.r_pad);
-    P.chk.alloc(nvec * P.n_pad);
+    if (!P.cheb) P.chk.alloc(nvec * P.n_pad);
     if (P.m2l_form) P.ut_bf.alloc(m2l_split_vecs_elems(P.r_pad, (int64_t)nvec, m2l_form_parts(P.m2l_form)));
     P.phi_u.alloc(nvec * P.n_pad);
     P.phi_d.alloc(nvec * P.n_pad);
@@ -241,6 +244,8 @@ int fmm_setup(const float *src_xyz, const float *src_nrm, int64_t n_src, const f
         h->p.reset(new Plan());
         try {
             Plan &P = *h->p;
+            Arena temp;
+            ArenaScope scope(&P.mem, &temp);
             init_plan(P, opt);
             P.leaf_from_cache = from_cache;
             build_tree(P.t, src_xyz, src_nrm, n_src, trg_xyz, trg_nrm, n_trg, tree_options(opt), s);
@@ -290,6 +295,8 @@ int fmm_setup_batch(int n_inst, const int64_t *src_off, const int64_t *trg_off, 
         h->p.reset(new Plan());
         try {
             Plan &P = *h->p;
+            Arena temp;
+            ArenaScope scope(&P.mem, &temp);
             init_plan(P, opt);
             P.leaf_from_cache = from_cache;
             build_forest(P.t, so, to, src_xyz, src_nrm, tsm ? trg_xyz : nullptr, trg_nrm, tree_options(opt), s);
@@ -480,27 +487,30 @@ int fmm_export_tree(fmm_plan plan, const fmm_tree_export *o) {
         Plan &P = live(plan);
         FMM_REQUIRE(o != nullptr, "fmm_export_tree: out is NULL");
         Tree &t = P.t;
+        hipStream_t s = nullptr;
         auto cp = [](auto *dst, const auto &src) {
             if (dst) std::copy(src.begin(), src.end(), dst);
+        };
+        auto cpd = [&](auto *dst, const auto &src, int64_t n) {
+            if (dst && n) d2h(dst, src.p, n, s);
         };
         cp(o->level, t.h_level);
         cp(o->anchor, t.h_anchor);
         cp(o->parent, t.h_parent);
-        cp(o->begin, t.h_begin);
-        cp(o->end, t.h_end);
+        cpd(o->begin, t.begin, t.nb);
+        cpd(o->end, t.end, t.nb);
         cp(o->tbeg, t.h_tbeg);
         cp(o->tend, t.h_tend);
         cp(o->sbeg, t.h_sbeg);
         cp(o->send, t.h_send);
         cp(o->u_off, t.U.h_off);
         cp(o->u_idx, t.U.h_idx);
-        cp(o->v_off, t.V.h_off);
-        cp(o->v_idx, t.V.h_idx);
+        cpd(o->v_off, t.V.off, t.nb ? t.nb + 1 : 0);
+        cpd(o->v_idx, t.V.idx, t.V.total);
         cp(o->w_off, t.W.h_off);
         cp(o->w_idx, t.W.h_idx);
         cp(o->x_off, t.X.h_off);
         cp(o->x_idx, t.X.h_idx);
-        hipStream_t s = nullptr;
         if (o->src_perm && t.n_src) d2h(o->src_perm, t.src_perm.p, t.n_src, s);
         if (o->trg_perm && t.n_trg) d2h(o->trg_perm, t.tsm ? t.trg_perm.p : t.src_perm.p, t.n_trg, s);
         if (o->keys && t.n) d2h(o->keys, t.keys.p, t.n, s);

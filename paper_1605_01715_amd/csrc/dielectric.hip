@@ -98,7 +98,7 @@ void charge_field(Plan &P, const float *sigma, const float *sigma2, const float 
     DBuf<float> dens(n);
     field.alloc(3 * n);
     charge_field_into(P, sigma, sigma2, areas, dens.p, field.p, s);
-    FMM_HIP(hipStreamSynchronize(s));  // dens is freed on return
+    if (!dens.home) FMM_HIP(hipStreamSynchronize(s));  // dens is freed on return
 }
 
 void launch_rhs(const Plan &P, const float *field, const float *sigma_f, const float *areas, const float *curv,
@@ -117,6 +117,8 @@ void dielectric_rhs(Plan &P, const float *sigma_f, const float *areas, const flo
     require_field_plan(P, "fmm_dielectric_rhs");
     const int64_t n = P.t.n_src;
     if (n == 0) return;
+    Arena mem;  // the call's buffers
+    ArenaScope scope(&mem, &mem);
     DBuf<float> field;
     charge_field(P, sigma_f, nullptr, areas, field, s);
     launch_rhs(P, field.p, sigma_f, areas, curv, eps_i, eps_m, e0, b, s);
@@ -182,6 +184,8 @@ void body_forces(Plan &P, const float *sigma, const float *sigma2, const float *
     FMM_REQUIRE(body_off[0] == 0 && body_off[n_body] == n, "fmm_body_forces: body offsets must span 0..n");
     for (int i = 0; i < n_body; ++i)
         FMM_REQUIRE(body_off[i + 1] >= body_off[i], "fmm_body_forces: body offsets must be nondecreasing");
+    Arena mem;  // the call's buffers
+    ArenaScope scope(&mem, &mem);
     DBuf<float> field;
     if (n) charge_field(P, sigma, sigma2, areas, field, s);
     std::vector<int64_t> off(body_off, body_off + n_body + 1);

@@ -190,6 +190,8 @@ struct Gmres {
 
 void plan_gmres(Plan &P, const fmm_operator &op, const double *b, double *x, double rtol, int restart, int max_iter,
                 int *iters_out, double *rel_out, int *status, hipStream_t s) {
+    Arena mem;  // the call's buffers
+    ArenaScope scope(&mem, &mem);
     Gmres G(P, op, restart, s);
     const int64_t n = G.n;
     const int m = restart;

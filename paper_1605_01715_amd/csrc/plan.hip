@@ -285,6 +285,7 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
     };
     Tree &t = P.t;
     Lap wl;
+    Transfers tr;  // flushed before the kernel that needs a list, and at the end
     const int64_t nb = t.nb;
     const int nrhs = P.nrhs, ns = P.ns;
     auto nsrc = [&](int64_t b) { return t.h_send[b] - t.h_sbeg[b]; };
@@ -298,7 +299,7 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         std::vector<double> sc((size_t)nb * nrhs);
         for (int64_t b = 0; b < nb; ++b)
             for (int r = 0; r < nrhs; ++r) sc[b * nrhs + r] = t.h_half[b];
-        P.col_scale = upload(sc, s);
+        tr.up(P.col_scale, std::move(sc));
     }
 
     // P2M
@@ -312,14 +313,14 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
                 P.p2m_evals += nsrc(b) * ns;
             }
         P.n_p2m = (int)items.size();
-        P.p2m_items = upload(items, s);
-        P.p2m_roff = upload(roff, s);
-        P.p2m_rng = upload(rng, s);
+        tr.up(P.p2m_items, items);
+        tr.up(P.p2m_roff, roff);
+        tr.up(P.p2m_rng, rng);
         GemmJob &j = P.p2m_proj;
         std::vector<int32_t> cols = tile_columns(items, nrhs, kGemmCols, j.ntile);
         j.nterm = 1;
-        j.cols = upload(cols, s);
-        j.src = upload(cols, s);
+        tr.up(j.cols, cols);
+        tr.up(j.src, cols);
     }
 
     wl("scales and P2M lists");
@@ -344,8 +345,8 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
                     if (ch >= 0 && nsrc(ch) > 0) src[((size_t)tl * 8 + o) * ncol64 + c] = ch * nrhs + r;
                 }
             }
-        j.cols = upload(cols, s);
-        j.src = upload(src, s);
+        tr.up(j.cols, cols);
+        tr.up(j.src, src);
         P.m2m_jobs.push_back(std::move(j));
     }
 
@@ -359,7 +360,7 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         // words in order compares the sets lexicographically)
         std::vector<uint64_t> mask((size_t)nb * kMaskWords);
         {
-            DBuf<uint64_t> dm(mask.size());
+            DBuf<uint64_t> dm(mask.size(), Temp{});
             hipLaunchKernelGGL(k_dir_masks, dim3(grid_for(nb, kBlock / 64)), dim3(kBlock), 0, s, t.vdense.p, nb,
                                t.sbeg.p, t.send.p, dm.p);
             FMM_HIP(hipGetLastError());
@@ -672,13 +673,13 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             cols.swap(cols2);
             ntile = (int)(8 * len);
             lap("m2l pieces");
-            P.m2l_slot = upload(slot2, s);
+            tr.up(P.m2l_slot, std::move(slot2));
             P.m2l_nsplit = (int)red_k.size();
             if (nslot > 0) P.m2l_partial.alloc((size_t)nslot * nc * P.r_pad);
             if (P.m2l_nsplit > 0) {
-                P.m2l_red_cols = upload(red_cols, s);
-                P.m2l_red_slot0 = upload(red_slot0, s);
-                P.m2l_red_k = upload(red_k, s);
+                tr.up(P.m2l_red_cols, std::move(red_cols));
+                tr.up(P.m2l_red_slot0, std::move(red_slot0));
+                tr.up(P.m2l_red_k, std::move(red_k));
             }
             // pair tiles: per target vector, its partial rows in direction
             // order. The pair tiles were made in increasing direction, so they
@@ -702,35 +703,35 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             P.m2l_ngather = (int)gt.size();
             P.m2l_pair_tiles = (int)std::count(pair_tile.begin(), pair_tile.end(), 1);
             if (P.m2l_ngather > 0) {
-                P.m2l_gt = upload(gt, s);
-                P.m2l_goff = upload(goff, s);
-                P.m2l_gidx = upload(gidx, s);
+                tr.up(P.m2l_gt, std::move(gt));
+                tr.up(P.m2l_goff, std::move(goff));
+                tr.up(P.m2l_gidx, std::move(gidx));
             }
         }
-        lap("m2l uploads");
         P.m2l_ntile = ntile;
         P.m2l_steps = (int64_t)tdir.size();
         P.m2l_ncol = nc;
-        P.m2l_toff = upload(toff, s);
-        P.m2l_dir = upload(tdir, s);
-        P.m2l_cols = upload(cols, s);
         // the source vector of every (step, column), filled on the device
-        {
-            std::vector<int32_t> item(tdir.size());
-            for (int k = 0; k < ntile; ++k)
-                std::fill(item.begin() + toff[k], item.begin() + toff[k + 1], (int32_t)k);
-            DBuf<int32_t> ditem = upload(item, s);
-            P.m2l_src.alloc(tdir.size() * (size_t)nc);
-            const int64_t n = (int64_t)tdir.size() * nc;
-            if (n > 0) {
-                hipLaunchKernelGGL(k_m2l_sources, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, ditem.p,
-                                   P.m2l_dir.p, (int64_t)tdir.size(), P.m2l_cols.p, nc, t.vdense.p, t.sbeg.p,
-                                   t.send.p, nrhs, P.m2l_src.p);
-                FMM_HIP(hipGetLastError());
-            }
-            FMM_HIP(hipStreamSynchronize(s));
+        const int64_t nstep = (int64_t)tdir.size();
+        std::vector<int32_t> item(tdir.size());
+        for (int k = 0; k < ntile; ++k)
+            std::fill(item.begin() + toff[k], item.begin() + toff[k + 1], (int32_t)k);
+        DBuf<int32_t> ditem;
+        tr.up(ditem, std::move(item));
+        tr.up(P.m2l_toff, std::move(toff));
+        tr.up(P.m2l_dir, std::move(tdir));
+        tr.up(P.m2l_cols, std::move(cols));
+        tr.up(P.m2l_zero, std::vector<float>(48, 0.f));
+        tr.flush_up(s);
+        lap("m2l uploads");
+        P.m2l_src.alloc((size_t)nstep * nc);
+        if (nstep > 0) {
+            hipLaunchKernelGGL(k_m2l_sources, dim3(grid_for(nstep * nc, kBlock)), dim3(kBlock), 0, s, ditem.p,
+                               P.m2l_dir.p, nstep, P.m2l_cols.p, nc, t.vdense.p, t.sbeg.p, t.send.p, nrhs,
+                               P.m2l_src.p);
+            FMM_HIP(hipGetLastError());
         }
-        P.m2l_zero = upload(std::vector<float>(48, 0.f), s);
+        if (!ditem.home) FMM_HIP(hipStreamSynchronize(s));  // freed on return
         lap("m2l sources");
     }
     phase_end(5);
@@ -759,16 +760,16 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             std::vector<int8_t> add((size_t)nb * nrhs, 0);
             for (int32_t b : items)
                 for (int r = 0; r < nrhs; ++r) add[(size_t)b * nrhs + r] = 1;
-            P.expand_add = upload(add, s);
+            tr.up(P.expand_add, add);
         }
-        P.p2l_items = upload(items, s);
-        P.p2l_roff = upload(roff, s);
-        P.p2l_rng = upload(rng, s);
+        tr.up(P.p2l_items, items);
+        tr.up(P.p2l_roff, roff);
+        tr.up(P.p2l_rng, rng);
         GemmJob &j = P.p2l_proj;
         std::vector<int32_t> cols = tile_columns(items, nrhs, kGemmCols, j.ntile);
         j.nterm = 1;
-        j.cols = upload(cols, s);
-        j.src = upload(cols, s);
+        tr.up(j.cols, cols);
+        tr.up(j.src, cols);
     }
 
     wl("P2L lists");
@@ -800,9 +801,9 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             j.ntile += nt;
         }
         if (j.ntile == 0) continue;
-        j.cols = upload(cols, s);
-        j.src = upload(src, s);
-        j.mat = upload(mat, s);
+        tr.up(j.cols, cols);
+        tr.up(j.src, src);
+        tr.up(j.mat, mat);
         P.l2l_jobs.push_back(std::move(j));
     }
 
@@ -846,8 +847,9 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
                             const DBuf<float> &x, const DBuf<float> &y, const DBuf<float> &z) {
             std::vector<float> h(6 * list.size());
             if (list.empty()) return h;
-            DBuf<int32_t> dl = upload(list, s);
-            DBuf<float> out(h.size());
+            DBuf<int32_t> dl(list.size(), Temp{});
+            h2d(dl.p, list.data(), list.size(), s);
+            DBuf<float> out(h.size(), Temp{});
             hipLaunchKernelGGL(k_point_boxes, dim3((unsigned)list.size()), dim3(64), 0, s, dl.p, beg.p, end.p, x.p,
                                y.p, z.p, out.p);
             FMM_HIP(hipGetLastError());
@@ -967,26 +969,26 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         }
         so[nb] = cs;
         po[nb] = cp;
-        P.soff = upload(so, s);
-        P.poff = upload(po, s);
-        P.pmid = upload(pm, s);
+        tr.up(P.soff, std::move(so));
+        tr.up(P.poff, std::move(po));
+        tr.up(P.pmid, std::move(pm));
         P.p2p_tested = tested_pairs;
     }
     wl("evaluation offsets");
     P.nwork = (int)wleaf.size();
-    P.wleaf = upload(wleaf, s);
-    P.wt0 = upload(wt0, s);
-    P.sbox = upload(sbox, s);
-    P.skind = upload(skind, s);
+    tr.up(P.wleaf, std::move(wleaf));
+    tr.up(P.wt0, std::move(wt0));
+    tr.up(P.sbox, std::move(sbox));
+    tr.up(P.skind, std::move(skind));
     prng.insert(prng.end(), 8, 0);  // the evaluation reads bounds up to 8 entries ahead
-    P.prng = upload(prng, s);
-    P.pcum = upload(pcum, s);
+    tr.up(P.prng, std::move(prng));
+    tr.up(P.pcum, std::move(pcum));
     {
         GemmJob &j = P.c2e_down;
         std::vector<int32_t> cols = tile_columns(down_boxes, nrhs, ncol64, j.ntile);
         j.nterm = 1;
-        j.cols = upload(cols, s);
-        j.src = upload(cols, s);
+        tr.up(j.cols, cols);
+        tr.up(j.src, cols);
     }
     {
         std::vector<int32_t> ub;
@@ -995,8 +997,8 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         GemmJob &j = P.c2e_up;
         std::vector<int32_t> cols = tile_columns(ub, nrhs, ncol64, j.ntile);
         j.nterm = 1;
-        j.cols = upload(cols, s);
-        j.src = upload(cols, s);
+        tr.up(j.cols, cols);
+        tr.up(j.src, cols);
     }
     if (P.cheb) {
         for (int l = t.nlev - 2; l >= 2; --l) {
@@ -1012,8 +1014,8 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             if (dst.empty()) continue;
             ChebJob j;
             j.n = (int)dst.size();
-            j.dst = upload(dst, s);
-            j.src = upload(src, s);
+            tr.up(j.dst, dst);
+            tr.up(j.src, src);
             P.cheb_m2m.push_back(std::move(j));
         }
         for (int l = 3; l < t.nlev; ++l) {
@@ -1029,9 +1031,9 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             if (dst.empty()) continue;
             ChebJob j;
             j.n = (int)dst.size();
-            j.dst = upload(dst, s);
-            j.src = upload(src, s);
-            j.oct = upload(oct, s);
+            tr.up(j.dst, dst);
+            tr.up(j.src, src);
+            tr.up(j.oct, oct);
             P.cheb_l2l.push_back(std::move(j));
         }
         std::vector<int32_t> with_src, with_trg;
@@ -1044,10 +1046,11 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             GemmJob &j = *jb;
             std::vector<int32_t> cols = tile_columns(jb == &P.cheb_compress ? with_src : with_trg, nrhs, ncol64, j.ntile);
             j.nterm = 1;
-            j.cols = upload(cols, s);
-            j.src = upload(cols, s);
+            tr.up(j.cols, cols);
+            tr.up(j.src, cols);
         }
     }
+    tr.flush_up(s);
     wl("evaluation uploads, expansion and Chebyshev lists");
     phase_end(6);
 }

@@ -29,6 +29,7 @@ struct GemmJob {
 enum Stage { ST_P2M = 0, ST_M2M, ST_P2L, ST_M2L, ST_L2L, ST_C2E, ST_EVAL, ST_COUNT };
 
 struct Plan {
+    Arena mem;  // every buffer of the plan (destroyed last)
     fmm_options opt{};
     int nrhs = 1;
     int n_inst = 1;  // independent instances (fmm_setup_batch)

@@ -6,7 +6,108 @@
 // function of the input.
 #include "common.hpp"
 
+#include <mutex>
+
 namespace fmm {
+
+namespace {
+
+struct Kept {
+    Block b;
+    int age = 0;  // arenas ended since it was given back
+};
+constexpr size_t kPoolBytes = size_t(512) << 20;
+constexpr int kPoolAge = 8;
+std::mutex g_pool_mu;
+// never destroyed: the HIP runtime may be gone when static objects end
+std::vector<Kept> &pool() {
+    static auto *v = new std::vector<Kept>();
+    return *v;
+}
+size_t g_pool_held = 0;
+
+// frees the kept blocks that `drop` names; the lock is held
+template <class F>
+void pool_drop(F &&drop) {
+    auto &v = pool();
+    size_t w = 0;
+    for (const Kept &k : v) {
+        if (drop(k)) {
+            g_pool_held -= k.b.bytes;
+            (void)hipFree(k.b.p);
+        } else {
+            v[w++] = k;
+        }
+    }
+    v.resize(w);
+}
+
+}  // namespace
+
+void *device_malloc(size_t bytes) {
+    void *p = nullptr;
+    hipError_t e = hipMalloc(&p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        {
+            std::lock_guard<std::mutex> lk(g_pool_mu);
+            pool_drop([](const Kept &) { return true; });
+        }
+        e = hipMalloc(&p, bytes);
+    }
+    if (e != hipSuccess) {
+        (void)hipDeviceSynchronize();
+        FMM_HIP(e);
+    }
+    return p;
+}
+
+Block block_take(size_t bytes) {
+    Block b;
+    FMM_HIP(hipGetDevice(&b.dev));
+    {
+        // the smallest kept block that fits without wasting a quarter
+        std::lock_guard<std::mutex> lk(g_pool_mu);
+        auto &v = pool();
+        size_t best = v.size();
+        for (size_t i = 0; i < v.size(); ++i) {
+            const Block &k = v[i].b;
+            if (k.dev == b.dev && k.bytes >= bytes && k.bytes <= bytes + bytes / 4 &&
+                (best == v.size() || k.bytes < v[best].b.bytes))
+                best = i;
+        }
+        if (best < v.size()) {
+            b = v[best].b;
+            g_pool_held -= b.bytes;
+            v.erase(v.begin() + (ptrdiff_t)best);
+            return b;
+        }
+    }
+    b.p = device_malloc(bytes);
+    b.bytes = bytes;
+    return b;
+}
+
+void block_give(const Block &b) {
+    {
+        std::lock_guard<std::mutex> lk(g_pool_mu);
+        if (g_pool_held + b.bytes <= kPoolBytes) {
+            try {
+                pool().push_back({b, 0});
+                g_pool_held += b.bytes;
+                return;
+            } catch (const std::bad_alloc &) {
+            }
+        }
+    }
+    (void)hipFree(b.p);
+}
+
+void block_pool_tick() {
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    for (Kept &k : pool()) ++k.age;
+    pool_drop([](const Kept &k) { return k.age > 2 * kPoolAge; });  // a setup ends two arenas
+}
 
 namespace {
 
@@ -43,7 +144,8 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_sums(const T *in, int64_t
 }
 
 template <class T>
-__global__ __launch_bounds__(kScanThreads) void k_tile_scan(const T *in, T *out, int64_t n, const T *offsets) {
+__global__ __launch_bounds__(kScanThreads) void k_tile_scan(const T *in, T *out, int64_t n, const T *offsets,
+                                                            T *total) {
     __shared__ T sh[kScanThreads];
     int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     T v[kScanItems];
@@ -57,38 +159,42 @@ __global__ __launch_bounds__(kScanThreads) void k_tile_scan(const T *in, T *out,
     for (int i = 0; i < kScanItems; ++i) {
         if (base + i < n) out[base + i] = run;
         run += v[i];
+        if (total && base + i == n - 1) *total = run;
     }
 }
 
+// total (may be NULL): receives the sum of all values, on the device
 template <class T>
-void scan_impl(const T *in, T *out, int64_t n, hipStream_t s) {
+void scan_impl(const T *in, T *out, int64_t n, T *total, hipStream_t s) {
     if (n <= 0) return;
     int64_t nt = (n + kScanTile - 1) / kScanTile;
     if (nt == 1) {
-        hipLaunchKernelGGL(k_tile_scan<T>, dim3(1), dim3(kScanThreads), 0, s, in, out, n, (const T *)nullptr);
+        hipLaunchKernelGGL(k_tile_scan<T>, dim3(1), dim3(kScanThreads), 0, s, in, out, n, (const T *)nullptr, total);
         FMM_HIP(hipGetLastError());
         return;
     }
-    DBuf<T> sums(nt);
+    DBuf<T> sums(nt, Temp{});
     hipLaunchKernelGGL(k_tile_sums<T>, dim3((unsigned)nt), dim3(kScanThreads), 0, s, in, n, sums.p);
     FMM_HIP(hipGetLastError());
-    scan_impl<T>(sums.p, sums.p, nt, s);
+    scan_impl<T>(sums.p, sums.p, nt, nullptr, s);
     hipLaunchKernelGGL(k_tile_scan<T>, dim3((unsigned)nt), dim3(kScanThreads), 0, s, in, out, n,
-                       (const T *)sums.p);
+                       (const T *)sums.p, total);
     FMM_HIP(hipGetLastError());
-    FMM_HIP(hipStreamSynchronize(s));  // `sums` is freed on return
+    if (!sums.home) FMM_HIP(hipStreamSynchronize(s));  // `sums` is freed on return
 }
 
 template <class T>
 T scan_total(const T *in, T *out, int64_t n, hipStream_t s, bool want_total) {
     if (n <= 0) return 0;
-    T last_in = 0;
-    if (want_total) d2h(&last_in, in + (n - 1), 1, s);
-    scan_impl<T>(in, out, n, s);
-    if (!want_total) return 0;
-    T last_out = 0;
-    d2h(&last_out, out + (n - 1), 1, s);
-    return last_out + last_in;
+    if (!want_total) {
+        scan_impl<T>(in, out, n, nullptr, s);
+        return 0;
+    }
+    DBuf<T> total(1, Temp{});
+    scan_impl<T>(in, out, n, total.p, s);
+    T h = 0;
+    d2h(&h, total.p, 1, s);
+    return h;
 }
 
 // ---------------------------------------------------------------- radix sort
@@ -156,11 +262,54 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(const uint64_t *kin, 
 
 }  // namespace
 
+void Transfers::flush(bool up, hipStream_t s) {
+    constexpr size_t kLarge = size_t(1) << 20;
+    const hipMemcpyKind kind = up ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost;
+    auto copy = [&](char *dev, char *host, size_t bytes) {
+        FMM_HIP(hipMemcpyAsync(up ? dev : host, up ? host : dev, bytes, kind, s));
+    };
+    std::vector<std::vector<char>> held;  // host buffers in flight
+    struct Part {
+        size_t run;
+        size_t first, last;  // items [first, last)
+    };
+    std::vector<Part> parts;
+    for (size_t i = 0; i < items_.size();) {
+        if (items_[i].bytes > kLarge) {
+            copy(items_[i].dev, items_[i].host, items_[i].bytes);
+            ++i;
+            continue;
+        }
+        size_t j = i + 1;
+        const char *end = items_[i].dev + items_[i].bytes;
+        // the next buffer starts within the padding of the last one's end
+        while (j < items_.size() && items_[j].bytes <= kLarge && items_[j].dev >= end && items_[j].dev - end < 256) {
+            end = items_[j].dev + items_[j].bytes;
+            ++j;
+        }
+        held.emplace_back((size_t)(end - items_[i].dev));
+        char *h = held.back().data();
+        if (up)
+            for (size_t k = i; k < j; ++k) std::memcpy(h + (items_[k].dev - items_[i].dev), items_[k].host, items_[k].bytes);
+        copy(items_[i].dev, h, held.back().size());
+        if (!up) parts.push_back({held.size() - 1, i, j});
+        i = j;
+    }
+    FMM_HIP(hipStreamSynchronize(s));
+    for (const Part &p : parts)
+        for (size_t k = p.first; k < p.last; ++k)
+            std::memcpy(items_[k].host, held[p.run].data() + (items_[k].dev - items_[p.first].dev), items_[k].bytes);
+    items_.clear();
+}
+
 int64_t exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t n, hipStream_t s, bool want_total) {
     return scan_total<int64_t>(in, out, n, s, want_total);
 }
 int64_t exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, hipStream_t s, bool want_total) {
     return scan_total<int32_t>(in, out, n, s, want_total);
+}
+void exclusive_scan_i32_total(const int32_t *in, int32_t *out, int64_t n, int32_t *total, hipStream_t s) {
+    scan_impl<int32_t>(in, out, n, total, s);
 }
 uint32_t exclusive_scan_u32(const uint32_t *in, uint32_t *out, int64_t n, hipStream_t s, bool want_total) {
     return scan_total<uint32_t>(in, out, n, s, want_total);
@@ -170,9 +319,9 @@ void radix_sort_pairs(uint64_t *keys, int64_t *vals, int64_t n, int bits, hipStr
     if (n <= 1) return;
     FMM_REQUIRE(n < (int64_t(1) << 31), "radix sort: more than 2^31 - 1 points");
     int nblk = (int)((n + kRsTile - 1) / kRsTile);
-    DBuf<uint64_t> k2(n);
-    DBuf<int64_t> v2(n);
-    DBuf<uint32_t> hist((size_t)256 * nblk);
+    DBuf<uint64_t> k2(n, Temp{});
+    DBuf<int64_t> v2(n, Temp{});
+    DBuf<uint32_t> hist((size_t)256 * nblk, Temp{});
     uint64_t *ka = keys, *kb = k2.p;
     int64_t *va = vals, *vb = v2.p;
     int passes = (bits + 7) / 8;
@@ -180,7 +329,7 @@ void radix_sort_pairs(uint64_t *keys, int64_t *vals, int64_t n, int bits, hipStr
         int shift = 8 * ps;
         hipLaunchKernelGGL(k_rs_hist, dim3(nblk), dim3(kRsThreads), 0, s, ka, n, shift, hist.p, nblk);
         FMM_HIP(hipGetLastError());
-        scan_impl<uint32_t>(hist.p, hist.p, (int64_t)256 * nblk, s);
+        scan_impl<uint32_t>(hist.p, hist.p, (int64_t)256 * nblk, nullptr, s);
         hipLaunchKernelGGL(k_rs_scatter, dim3(nblk), dim3(kRsThreads), 0, s, ka, va, kb, vb, n, shift,
                            hist.p, nblk);
         FMM_HIP(hipGetLastError());
@@ -191,7 +340,7 @@ void radix_sort_pairs(uint64_t *keys, int64_t *vals, int64_t n, int bits, hipStr
         FMM_HIP(hipMemcpyAsync(keys, ka, n * sizeof(uint64_t), hipMemcpyDeviceToDevice, s));
         FMM_HIP(hipMemcpyAsync(vals, va, n * sizeof(int64_t), hipMemcpyDeviceToDevice, s));
     }
-    FMM_HIP(hipStreamSynchronize(s));
+    if (!k2.home) FMM_HIP(hipStreamSynchronize(s));  // the temporaries are freed on return
 }
 
 }  // namespace fmm

@@ -83,7 +83,7 @@ bool bbox(const float *a, int64_t n, hipStream_t s, double lo[3], double hi[3]) 
     for (int c = 0; c < 3; ++c) { lo[c] = INFINITY; hi[c] = -INFINITY; }
     if (n == 0) return true;
     int nblk = (int)std::min<int64_t>(1024, (n + kBlock - 1) / kBlock);
-    DBuf<float> part((size_t)8 * nblk);
+    DBuf<float> part((size_t)8 * nblk, Temp{});
     hipLaunchKernelGGL(k_bbox_finite, dim3(nblk), dim3(kBlock), 0, s, a, n, part.p);
     FMM_HIP(hipGetLastError());
     std::vector<float> h((size_t)8 * nblk);
@@ -199,7 +199,7 @@ __global__ void k_difflevel(const uint64_t *key, const int32_t *sinst, int64_t n
 
 __global__ void k_split_flags(const int32_t *pbox, const uint8_t *dl, const int64_t *cbeg, const int64_t *cend,
                               int64_t n, int lvl, int uniform_depth, int leaf_size, int max_depth,
-                              int32_t *flag) {
+                              int32_t *flag, int32_t *start) {
     int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
     int32_t b = pbox[i];
@@ -213,6 +213,7 @@ __global__ void k_split_flags(const int32_t *pbox, const uint8_t *dl, const int6
         if (split) f |= 2;
     }
     flag[i] = f;
+    start[i] = f & 1;  // scanned into child indices
 }
 
 __global__ void k_children(const int32_t *flag, const int32_t *cidx, const int32_t *pbox, int64_t n,
@@ -235,11 +236,6 @@ __global__ void k_child_end(const int64_t *nbeg, const int32_t *nparent, const i
     if (c >= nc) return;
     bool same = (c + 1 < nc) && nparent[c + 1] == nparent[c];
     nend[c] = same ? nbeg[c + 1] : cend[nparent[c]];
-}
-
-__global__ void k_strip_flag(int32_t *flag, int64_t n) {
-    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) flag[i] &= 1;
 }
 
 // assemble one level's boxes into the global arrays; a box's root cube is its
@@ -549,19 +545,12 @@ __global__ __launch_bounds__(kBlock) void k_sort_segments(const int32_t *off, co
     }
 }
 
-void csr_from_counts(Csr &l, DBuf<int32_t> &cnt, int64_t nb, hipStream_t s) {
+// offsets of a list from its counts; its length goes to *total on the device
+void csr_offsets(Csr &l, DBuf<int32_t> &cnt, int64_t nb, int32_t *total, hipStream_t s) {
     l.off.alloc(nb + 1);
-    FMM_HIP(hipMemsetAsync(l.off.p + nb, 0, sizeof(int32_t), s));
     FMM_HIP(hipMemcpyAsync(l.off.p, cnt.p, nb * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-    l.total = exclusive_scan_i32(l.off.p, l.off.p, nb + 1, s, true);
-    l.idx.alloc(std::max<int64_t>(l.total, 1));
-}
-
-void csr_to_host(Csr &l, int64_t nb, hipStream_t s) {
-    l.h_off.resize(nb + 1);
-    d2h(l.h_off.data(), l.off.p, nb + 1, s);
-    l.h_idx.resize(l.total);
-    d2h(l.h_idx.data(), l.idx.p, l.total, s);
+    exclusive_scan_i32_total(l.off.p, l.off.p, nb, total, s);
+    FMM_HIP(hipMemcpyAsync(l.off.p + nb, total, sizeof(int32_t), hipMemcpyDeviceToDevice, s));
 }
 
 }  // namespace
@@ -702,7 +691,7 @@ void build_any(Tree &t, const float *src, const float *src_nrm, int64_t n_src, c
                        dto.p, dso.p, t.keys.p, t.order.p, pinst.p);
     FMM_HIP(hipGetLastError());
     radix_sort_pairs(t.keys.p, t.order.p, n, 63, s);
-    DBuf<int32_t> pbox(n);
+    DBuf<int32_t> pbox(n, Temp{});
     // level 0: one root per instance with points, over its run of sorted points
     std::vector<int64_t> b0, e0;
     if (forest) {
@@ -718,8 +707,8 @@ void build_any(Tree &t, const float *src, const float *src_nrm, int64_t n_src, c
         }
         int bits = 1;
         while ((1 << bits) < ni) ++bits;
-        DBuf<uint64_t> ik(n), keys2(n);
-        DBuf<int64_t> pos(n), order2(n);
+        DBuf<uint64_t> ik(n, Temp{}), keys2(n);
+        DBuf<int64_t> pos(n, Temp{}), order2(n);
         hipLaunchKernelGGL(k_inst_keys, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, t.order.p, pinst.p, n, ik.p,
                            pos.p);
         FMM_HIP(hipGetLastError());
@@ -740,10 +729,10 @@ void build_any(Tree &t, const float *src, const float *src_nrm, int64_t n_src, c
     phase_end(0);
 
     // level-by-level build
-    DBuf<uint8_t> dl(n);
+    DBuf<uint8_t> dl(n, Temp{});
     hipLaunchKernelGGL(k_difflevel, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, t.keys.p, sinst.p, n, dl.p);
     FMM_HIP(hipGetLastError());
-    DBuf<int32_t> npbox(n), flag(n), cidx(n);
+    DBuf<int32_t> npbox(n, Temp{}), flag(n, Temp{}), cidx(n, Temp{});
     std::vector<DBuf<int64_t>> lbeg, lend;
     std::vector<DBuf<int32_t>> lpar;
     {
@@ -756,16 +745,12 @@ void build_any(Tree &t, const float *src, const float *src_nrm, int64_t n_src, c
     for (int lvl = 0; lvl < kMaxLevel; ++lvl) {
         hipLaunchKernelGGL(k_split_flags, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, pbox.p, dl.p,
                            lbeg[lvl].p, lend[lvl].p, n, lvl, opt.uniform_depth, opt.leaf_size, opt.max_depth,
-                           flag.p);
-        FMM_HIP(hipGetLastError());
-        // scan only the start bit: copy flags & 1 into cidx then scan
-        FMM_HIP(hipMemcpyAsync(cidx.p, flag.p, n * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-        hipLaunchKernelGGL(k_strip_flag, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, cidx.p, n);
+                           flag.p, cidx.p);
         FMM_HIP(hipGetLastError());
         int64_t nc = exclusive_scan_i32(cidx.p, cidx.p, n, s, true);
         if (nc == 0) break;
-        DBuf<int64_t> nbeg(nc), nend(nc);
-        DBuf<int32_t> npar(nc);
+        DBuf<int64_t> nbeg(nc, Temp{}), nend(nc, Temp{});
+        DBuf<int32_t> npar(nc, Temp{});
         hipLaunchKernelGGL(k_children, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, flag.p, cidx.p, pbox.p, n,
                            nbeg.p, npar.p, npbox.p);
         FMM_HIP(hipGetLastError());
@@ -783,16 +768,21 @@ void build_any(Tree &t, const float *src, const float *src_nrm, int64_t n_src, c
     for (int l = 0; l < t.nlev; ++l) t.lvl_off[l + 1] = t.lvl_off[l] + counts[l];
     const int64_t nb = t.nb = t.lvl_off[t.nlev];
 
-    t.level.alloc(nb);
-    t.parent.alloc(nb);
-    t.child.alloc(8 * nb);
-    t.anchor.alloc(3 * nb);
     t.bkey.alloc(nb);
     t.begin.alloc(nb);
     t.end.alloc(nb);
     t.centre.alloc(3 * nb);
+    // the arrays with host copies one after the other, for few transfers
+    t.level.alloc(nb);
+    t.parent.alloc(nb);
+    t.child.alloc(8 * nb);
+    t.anchor.alloc(3 * nb);
     t.half.alloc(nb);
     t.leaf.alloc(nb);
+    t.tbeg.alloc(nb);
+    t.tend.alloc(nb);
+    t.sbeg.alloc(nb);
+    t.send.alloc(nb);
     if (forest) t.binst.alloc(nb);
     FMM_HIP(hipMemsetAsync(t.child.p, 0xff, 8 * nb * sizeof(int32_t), s));
     for (int l = 0; l < t.nlev; ++l) {
@@ -807,10 +797,6 @@ void build_any(Tree &t, const float *src, const float *src_nrm, int64_t n_src, c
     FMM_HIP(hipGetLastError());
 
     // target / source ranges and sorted point data
-    t.tbeg.alloc(nb);
-    t.tend.alloc(nb);
-    t.sbeg.alloc(nb);
-    t.send.alloc(nb);
     t.src_perm.alloc(n_src);
     t.sx.alloc(n_src);
     t.sy.alloc(n_src);
@@ -821,7 +807,7 @@ void build_any(Tree &t, const float *src, const float *src_nrm, int64_t n_src, c
         t.snz.alloc(n_src);
     }
     if (t.tsm) {
-        DBuf<int64_t> ct(n + 1), cs(n + 1);
+        DBuf<int64_t> ct(n + 1, Temp{}), cs(n + 1, Temp{});
         hipLaunchKernelGGL(k_type_flags, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, t.order.p, n, n_trg,
                            ct.p, cs.p);
         FMM_HIP(hipGetLastError());
@@ -894,68 +880,70 @@ void build_any(Tree &t, const float *src, const float *src_nrm, int64_t n_src, c
     hipLaunchKernelGGL(k_vdense, dim3(grid_for(kNumDirs * nb, kBlock)), dim3(kBlock), 0, s, v, nb, t.vdense.p);
     FMM_HIP(hipGetLastError());
     {
-        DBuf<int32_t> cnt(nb);
-        hipLaunchKernelGGL(k_vcount, dim3(grid_boxes(nb)), dim3(kBlock), 0, s, t.vdense.p, nb, cnt.p);
+        // counts, offsets and lengths of V, U and W; X has W's length
+        DBuf<int32_t> vcnt(nb, Temp{}), ucnt(nb, Temp{}), wcnt(nb, Temp{}), len(4, Temp{});  // len[3]: stack overflow
+        FMM_HIP(hipMemsetAsync(len.p, 0, len.bytes(), s));
+        hipLaunchKernelGGL(k_vcount, dim3(grid_boxes(nb)), dim3(kBlock), 0, s, t.vdense.p, nb, vcnt.p);
         FMM_HIP(hipGetLastError());
-        csr_from_counts(t.V, cnt, nb, s);
-        hipLaunchKernelGGL(k_vfill, dim3(grid_boxes(nb)), dim3(kBlock), 0, s, t.vdense.p, nb, t.V.off.p,
-                           t.V.idx.p);
-        FMM_HIP(hipGetLastError());
-    }
-    {
-        DBuf<int32_t> ucnt(nb), wcnt(nb), ovf(1);
-        FMM_HIP(hipMemsetAsync(ovf.p, 0, sizeof(int32_t), s));
         hipLaunchKernelGGL(k_uw<false>, dim3(grid_for(nb, kBlock)), dim3(kBlock), 0, s, v, nb, ucnt.p, wcnt.p,
                            (const int32_t *)nullptr, (int32_t *)nullptr, (const int32_t *)nullptr,
-                           (int32_t *)nullptr, ovf.p);
+                           (int32_t *)nullptr, len.p + 3);
         FMM_HIP(hipGetLastError());
-        csr_from_counts(t.U, ucnt, nb, s);
-        csr_from_counts(t.W, wcnt, nb, s);
+        csr_offsets(t.V, vcnt, nb, len.p, s);
+        csr_offsets(t.U, ucnt, nb, len.p + 1, s);
+        csr_offsets(t.W, wcnt, nb, len.p + 2, s);
+        int32_t h_len[4];
+        d2h(h_len, len.p, 4, s);
+        if (h_len[3]) throw Error(FMM_ERR_DEVICE, "fmm_setup: list traversal stack overflow");
+        t.V.total = h_len[0];
+        t.U.total = h_len[1];
+        t.W.total = t.X.total = h_len[2];
+        auto room = [](const Csr &l) { return (size_t)std::max<int64_t>(l.total, 1); };
+        for (Csr *l : {&t.U, &t.V, &t.W, &t.X}) l->idx.alloc(room(*l));
+        // fill in any order, then sort
+        DBuf<int32_t> vraw(room(t.V), Temp{}), uraw(room(t.U), Temp{}), wraw(room(t.W), Temp{}),
+            xraw(room(t.X), Temp{}), xcnt(nb, Temp{}), xcur(nb, Temp{});
+        hipLaunchKernelGGL(k_vfill, dim3(grid_boxes(nb)), dim3(kBlock), 0, s, t.vdense.p, nb, t.V.off.p, vraw.p);
+        FMM_HIP(hipGetLastError());
         hipLaunchKernelGGL(k_uw<true>, dim3(grid_for(nb, kBlock)), dim3(kBlock), 0, s, v, nb, ucnt.p, wcnt.p,
-                           t.U.off.p, t.U.idx.p, t.W.off.p, t.W.idx.p, ovf.p);
+                           t.U.off.p, uraw.p, t.W.off.p, wraw.p, len.p + 3);
         FMM_HIP(hipGetLastError());
-        int32_t h_ovf = 0;
-        d2h(&h_ovf, ovf.p, 1, s);
-        if (h_ovf) throw Error(FMM_ERR_DEVICE, "fmm_setup: list traversal stack overflow");
-        // X = inverse of W
-        DBuf<int32_t> xcnt(nb), xcur(nb);
         FMM_HIP(hipMemsetAsync(xcnt.p, 0, nb * sizeof(int32_t), s));
         FMM_HIP(hipMemsetAsync(xcur.p, 0, nb * sizeof(int32_t), s));
-        hipLaunchKernelGGL(k_xcount, dim3(grid_boxes(nb)), dim3(kBlock), 0, s, t.W.off.p, t.W.idx.p, nb,
-                           xcnt.p);
+        hipLaunchKernelGGL(k_xcount, dim3(grid_boxes(nb)), dim3(kBlock), 0, s, t.W.off.p, wraw.p, nb, xcnt.p);
         FMM_HIP(hipGetLastError());
-        csr_from_counts(t.X, xcnt, nb, s);
-        hipLaunchKernelGGL(k_xfill, dim3(grid_boxes(nb)), dim3(kBlock), 0, s, t.W.off.p, t.W.idx.p, nb,
-                           t.X.off.p, xcur.p, t.X.idx.p);
+        csr_offsets(t.X, xcnt, nb, len.p, s);
+        hipLaunchKernelGGL(k_xfill, dim3(grid_boxes(nb)), dim3(kBlock), 0, s, t.W.off.p, wraw.p, nb, t.X.off.p,
+                           xcur.p, xraw.p);
         FMM_HIP(hipGetLastError());
+        auto sort = [&](Csr &l, DBuf<int32_t> &raw) {
+            hipLaunchKernelGGL(k_sort_segments, dim3(grid_boxes(nb)), dim3(kBlock), 0, s, l.off.p, raw.p, l.idx.p, nb);
+            FMM_HIP(hipGetLastError());
+        };
+        sort(t.V, vraw);
+        sort(t.U, uraw);
+        sort(t.W, wraw);
+        sort(t.X, xraw);
+        // host copies of the lists and box arrays that the work lists are made
+        // from (the others are exported from the device)
+        Transfers tr;
+        for (Csr *l : {&t.U, &t.W, &t.X}) {
+            tr.down(l->h_off, l->off, nb + 1);
+            tr.down(l->h_idx, l->idx, l->total);
+        }
+        auto box = [&](auto &h, const auto &d) { tr.down(h, d, d.n); };
+        box(t.h_level, t.level);
+        box(t.h_parent, t.parent);
+        box(t.h_child, t.child);
+        box(t.h_anchor, t.anchor);
+        box(t.h_half, t.half);
+        box(t.h_leaf, t.leaf);
+        box(t.h_tbeg, t.tbeg);
+        box(t.h_tend, t.tend);
+        box(t.h_sbeg, t.sbeg);
+        box(t.h_send, t.send);
+        tr.flush_down(s);
     }
-    for (Csr *l : {&t.U, &t.V, &t.W, &t.X}) {
-        DBuf<int32_t> sorted(l->idx.n);
-        hipLaunchKernelGGL(k_sort_segments, dim3(grid_boxes(nb)), dim3(kBlock), 0, s, l->off.p, l->idx.p, sorted.p, nb);
-        FMM_HIP(hipGetLastError());
-        std::swap(l->idx, sorted);
-        csr_to_host(*l, nb, s);
-    }
-
-    // host copies of the box arrays
-    auto cp32 = [&](std::vector<int32_t> &h, const DBuf<int32_t> &d) { h.resize(d.n); d2h(h.data(), d.p, d.n, s); };
-    auto cp64 = [&](std::vector<int64_t> &h, const DBuf<int64_t> &d) { h.resize(d.n); d2h(h.data(), d.p, d.n, s); };
-    cp32(t.h_level, t.level);
-    cp32(t.h_parent, t.parent);
-    cp32(t.h_child, t.child);
-    cp32(t.h_anchor, t.anchor);
-    cp64(t.h_begin, t.begin);
-    cp64(t.h_end, t.end);
-    cp64(t.h_tbeg, t.tbeg);
-    cp64(t.h_tend, t.tend);
-    cp64(t.h_sbeg, t.sbeg);
-    cp64(t.h_send, t.send);
-    t.h_leaf.resize(nb);
-    d2h(t.h_leaf.data(), t.leaf.p, nb, s);
-    t.h_centre.resize(3 * nb);
-    d2h(t.h_centre.data(), t.centre.p, 3 * nb, s);
-    t.h_half.resize(nb);
-    d2h(t.h_half.data(), t.half.p, nb, s);
     phase_end(2);
 }
 

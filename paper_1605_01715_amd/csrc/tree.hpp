@@ -17,7 +17,7 @@ struct TreeOptions {
 // CSR list: off[n_boxes + 1], idx[off[n_boxes]].
 struct Csr {
     DBuf<int32_t> off, idx;
-    std::vector<int32_t> h_off, h_idx;  // host copies
+    std::vector<int32_t> h_off, h_idx;  // host copies (not of V)
     int64_t total = 0;
 };
 
@@ -45,9 +45,9 @@ struct Tree {
 
     // host copies of the box arrays
     std::vector<int32_t> h_level, h_parent, h_child, h_anchor;
-    std::vector<int64_t> h_begin, h_end, h_tbeg, h_tend, h_sbeg, h_send;
+    std::vector<int64_t> h_tbeg, h_tend, h_sbeg, h_send;
     std::vector<uint8_t> h_leaf;
-    std::vector<double> h_centre, h_half;
+    std::vector<double> h_half;
 
     // lists
     DBuf<int32_t> colleague;  // [nb][27]
