@@ -263,90 +263,118 @@ __global__ __launch_bounds__(64) void k_nodes_to_points(const double *coef, Eval
 // out (+)= (A_x (x) A_y (x) A_z) in with A_c = S[side_c] (M2M) or its
 // transpose (L2L). Lane (q, s) = (lane / N, lane % N): the z pass gives
 // T1[p'][q][s] (to LDS), the y pass T2[p'] for the lane's (q, s) in
-// registers, the x pass accumulates out[p][q][s] for every p.
-template <int N, int NRHS, bool L2L>
-__global__ __launch_bounds__(64) void k_cheb_tensor(const double *s1, const int32_t *dst, const int32_t *src,
-                                                   const int8_t *oct, const float *in, float *out, int n_pad) {
+// registers, the x pass acc[p] for every p.
+//
+// M2M: one workgroup per (parent, right-hand side), one wave per child: a
+// level's few parents are bound by latency, and eight children in sequence in
+// one wave were eight times its chain of LDS passes. Waves share nothing until
+// the end, where the children's results are added in child order through LDS.
+// Measured, one wave per parent -> this: n = 8, 48 to 748 parents 14-19 -> 5-10
+// us a level; n = 5, two right-hand sides, 48 to 587 parents 18-20 -> 5-8 us; n =
+// 8, three right-hand sides, 8463 parents in three levels 230 -> 214 us.
+template <int N, bool L2L>
+__global__ __launch_bounds__(L2L ? 64 : 512) void k_cheb_tensor(const double *s1, const int32_t *dst,
+                                                               const int32_t *src, const int8_t *oct, int nrhs,
+                                                               const float *in, float *out, int n_pad) {
     constexpr int NN = N * N * N, NT = L2L ? 1 : 8;
     __shared__ double sm[2 * N * N];
-    __shared__ double X[NN], T1[NN];
-    const int lane = threadIdx.x, item = blockIdx.x;
-    for (int e = lane; e < 2 * N * N; e += 64) sm[e] = s1[e];
+    __shared__ __align__(16) float Xs[NT][NN];  // the child's values as stored; widened per use
+    __shared__ double T1s[NT][NN];
+    const int lane = threadIdx.x & 63, item = blockIdx.x, r = blockIdx.y;
+    const int t = NT == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float *X = Xs[t];
+    double *T1 = T1s[t];
+    for (int e = threadIdx.x; e < 2 * N * N; e += 64 * NT) sm[e] = s1[e];
     const bool act = lane < N * N;
     const int q = act ? lane / N : 0, sz = act ? lane % N : 0;
     // A_c[p][p'] from table side: S[side][p][p'] (M2M) or S[side][p'][p] (L2L)
     auto A = [&](int side, int p, int p2) { return L2L ? sm[(side * N + p2) * N + p] : sm[(side * N + p) * N + p2]; };
     const int64_t d = dst[item];
-#pragma unroll 1
-    for (int r = 0; r < NRHS; ++r) {
-        double acc[N];
+    const int64_t sb = src[(int64_t)item * NT + t];  // uniform across the wave
+    const int o = L2L ? oct[item] : t;
+    const int sx = (o >> 2) & 1, sy = (o >> 1) & 1, szd = o & 1;
+    if (sb >= 0) {
+        // all loads first, then the LDS writes, so the loads are in
+        // flight together rather than one latency each
+        constexpr int NV = (NN + 63) / 64;
+        float xv[NV];
 #pragma unroll
-        for (int p = 0; p < N; ++p) acc[p] = 0.0;
-#pragma unroll 1
-        for (int t = 0; t < NT; ++t) {
-            const int64_t sb = src[(int64_t)item * NT + t];
-            if (sb < 0) continue;  // uniform across the wave
-            const int o = L2L ? oct[item] : t;
-            const int sx = (o >> 2) & 1, sy = (o >> 1) & 1, szd = o & 1;
-            __syncthreads();  // sm loaded; the previous term is done with X and T1
-            {
-                // all loads first, then the LDS writes, so the loads are in
-                // flight together rather than one latency each
-                constexpr int NV = (NN + 63) / 64;
-                float xv[NV];
+        for (int i = 0; i < NV; ++i)  // clamped index: no branch per load
+            xv[i] = in[(sb * nrhs + r) * n_pad + min(lane + 64 * i, NN - 1)];
 #pragma unroll
-                for (int i = 0; i < NV; ++i)  // clamped index: no branch per load
-                    xv[i] = in[(sb * NRHS + r) * n_pad + min(lane + 64 * i, NN - 1)];
+        for (int i = 0; i < NV; ++i)
+            if (lane + 64 * i < NN) X[lane + 64 * i] = xv[i];
+    }
+    __syncthreads();
+    if (act && sb >= 0) {
+        // z pass: T1[p'][q][s] = sum_s' A_z[s][s'] X[p'][q][s']
+        double az[N];
 #pragma unroll
-                for (int i = 0; i < NV; ++i)
-                    if (lane + 64 * i < NN) X[lane + 64 * i] = xv[i];
-            }
-            __syncthreads();
-            if (act) {
-                // z pass: T1[p'][q][s] = sum_s' A_z[s][s'] X[p'][q][s']
-                double az[N];
+        for (int s2 = 0; s2 < N; ++s2) az[s2] = A(szd, sz, s2);
 #pragma unroll
-                for (int s2 = 0; s2 < N; ++s2) az[s2] = A(szd, sz, s2);
+        for (int p2 = 0; p2 < N; ++p2) {
+            double v = 0.0;
 #pragma unroll
-                for (int p2 = 0; p2 < N; ++p2) {
-                    double v = 0.0;
-#pragma unroll
-                    for (int s2 = 0; s2 < N; ++s2) v += az[s2] * X[(p2 * N + q) * N + s2];
-                    T1[(p2 * N + q) * N + sz] = v;
-                }
-            }
-            __syncthreads();
-            if (act) {
-                // y pass: T2[p'] = sum_q' A_y[q][q'] T1[p'][q'][s]
-                double ay[N], t2[N];
-#pragma unroll
-                for (int q2 = 0; q2 < N; ++q2) ay[q2] = A(sy, q, q2);
-#pragma unroll
-                for (int p2 = 0; p2 < N; ++p2) {
-                    double v = 0.0;
-#pragma unroll
-                    for (int q2 = 0; q2 < N; ++q2) v += ay[q2] * T1[(p2 * N + q2) * N + sz];
-                    t2[p2] = v;
-                }
-                // x pass: acc[p] += sum_p' A_x[p][p'] T2[p']
-#pragma unroll
-                for (int p = 0; p < N; ++p) {
-                    double v = acc[p];
-#pragma unroll
-                    for (int p2 = 0; p2 < N; ++p2) v += A(sx, p, p2) * t2[p2];
-                    acc[p] = v;
-                }
-            }
+            for (int s2 = 0; s2 < N; ++s2) v += az[s2] * (double)X[(p2 * N + q) * N + s2];
+            T1[(p2 * N + q) * N + sz] = v;
         }
-        if (act) {
+    }
+    __syncthreads();
+    double acc[N];
 #pragma unroll
-            for (int p = 0; p < N; ++p) {
-                float *o = out + (d * NRHS + r) * n_pad + (p * N + q) * N + sz;
-                *o = L2L ? (float)((double)*o + acc[p]) : (float)acc[p];
-            }
+    for (int p = 0; p < N; ++p) acc[p] = 0.0;
+    if (act && sb >= 0) {
+        // y pass: T2[p'] = sum_q' A_y[q][q'] T1[p'][q'][s]
+        double ay[N], t2[N];
+#pragma unroll
+        for (int q2 = 0; q2 < N; ++q2) ay[q2] = A(sy, q, q2);
+#pragma unroll
+        for (int p2 = 0; p2 < N; ++p2) {
+            double v = 0.0;
+#pragma unroll
+            for (int q2 = 0; q2 < N; ++q2) v += ay[q2] * T1[(p2 * N + q2) * N + sz];
+            t2[p2] = v;
+        }
+        // x pass: acc[p] += sum_p' A_x[p][p'] T2[p']
+#pragma unroll
+        for (int p = 0; p < N; ++p) {
+            double v = 0.0;
+#pragma unroll
+            for (int p2 = 0; p2 < N; ++p2) v += A(sx, p, p2) * t2[p2];
+            acc[p] = v;
+        }
+    }
+    float *op = out + (d * nrhs + r) * n_pad + lane;  // + p N^2
+    if constexpr (L2L) {
+        if (!act) return;
+#pragma unroll
+        for (int p = 0; p < N; ++p) op[p * N * N] = (float)((double)op[p * N * N] + acc[p]);
+    } else {
+        __syncthreads();  // every wave is done with its T1
+        if (act)
+#pragma unroll
+            for (int p = 0; p < N; ++p) T1[p * N * N + lane] = acc[p];  // zeros for a missing child
+        __syncthreads();
+        if (act && t < N) {  // wave t adds plane p = t
+            double v = 0.0;
+#pragma unroll
+            for (int c = 0; c < NT; ++c) v += T1s[c][t * N * N + lane];
+            op[t * N * N] = (float)v;
         }
     }
 }
+
+#define FMM_CHEB_N_SWITCH(N_VAR, CALL)                                   \
+    switch (N_VAR) {                                                     \
+    case 2: { constexpr int N = 2; CALL; } break;                        \
+    case 3: { constexpr int N = 3; CALL; } break;                        \
+    case 4: { constexpr int N = 4; CALL; } break;                        \
+    case 5: { constexpr int N = 5; CALL; } break;                        \
+    case 6: { constexpr int N = 6; CALL; } break;                        \
+    case 7: { constexpr int N = 7; CALL; } break;                        \
+    case 8: { constexpr int N = 8; CALL; } break;                        \
+    default: throw Error(FMM_ERR_ARG, "Chebyshev order must be 2..8");   \
+    }
 
 #define FMM_CHEB_SWITCH(N_VAR, NRHS_VAR, CALL)                                      \
     switch ((N_VAR) * 8 + (NRHS_VAR)) {                                             \
@@ -406,13 +434,13 @@ void cheb_tensor(int nrhs, int n, bool l2l, const double *s1, int nitems, const 
                  const int8_t *oct, const float *in, float *out, int n_pad, hipStream_t s) {
     if (nitems <= 0) return;
     FMM_REQUIRE(n_pad >= n * n * n, "cheb_tensor: rows shorter than n^3");
-    dim3 gr(nitems), bl(64);
+    const dim3 gr(nitems, nrhs);
     if (l2l) {
-        FMM_CHEB_SWITCH(n, nrhs, hipLaunchKernelGGL((k_cheb_tensor<N, R, true>), gr, bl, 0, s, s1, dst, src, oct, in,
-                                                    out, n_pad));
+        FMM_CHEB_N_SWITCH(n, hipLaunchKernelGGL((k_cheb_tensor<N, true>), gr, dim3(64), 0, s, s1, dst, src, oct, nrhs, in,
+                                                out, n_pad));
     } else {
-        FMM_CHEB_SWITCH(n, nrhs, hipLaunchKernelGGL((k_cheb_tensor<N, R, false>), gr, bl, 0, s, s1, dst, src, oct, in,
-                                                    out, n_pad));
+        FMM_CHEB_N_SWITCH(n, hipLaunchKernelGGL((k_cheb_tensor<N, false>), gr, dim3(512), 0, s, s1, dst, src, oct, nrhs,
+                                                in, out, n_pad));
     }
     FMM_HIP(hipGetLastError());
 }

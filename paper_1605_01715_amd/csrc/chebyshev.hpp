@@ -35,7 +35,7 @@ void nodes_to_points(int nrhs, int n, const double *coef, const EvalArgs &a, con
 // S[side][i][i'] = S(xbar_i, side / 2 + xbar_i' / 2) (side 0: -, 1: +) the map
 // from child o's node weights to the parent's is S[o_x] (x) S[o_y] (x) S[o_z]
 // (o_x = bit 2 of o, o_y bit 1, o_z bit 0), applied axis by axis (3 n^4
-// FMAs instead of n^6). One wave per item:
+// FMAs instead of n^6). One wave per item, right-hand side and source:
 //   M2M (l2l = false): out[dst[i]] = sum_{o < 8, src[8 i + o] >= 0} M_o in[src[8 i + o]]
 //   L2L (l2l = true):  out[dst[i]] += M_{oct[i]}^T in[src[i]]
 // Vectors are rows [(box * nrhs + r) * n_pad + m], s1 is [2][n][n] float64;
