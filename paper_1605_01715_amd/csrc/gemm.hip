@@ -299,6 +299,102 @@ __global__ __launch_bounds__(512) void k_gemm_f32(int m_pad, int k_pad, const in
     }
 }
 
+// The same product where there are too few tiles to fill the chip (a body of
+// 14,700 points has nine): the workgroups above are then bound by the latency
+// of one chain of k chunks, staging and barriers. Here a workgroup of eight
+// waves computes 8 / split blocks of 32 rows by 32 columns, the `split` waves
+// of a block share its k chunks, read both operands in fragment order straight
+// from global memory and add their partial sums in LDS in a fixed order.
+// Measured (tiles, rows x K), against one workgroup per tile: 9, 192 x 512 26 ->
+// 6 us; 9, 512 x 192 20 -> 5.5 us; 261, 192 x 512 38 -> 25 us; 382, 160 x 512 37 ->
+// 31 us.
+constexpr int kF32Waves = 8;
+__global__ __launch_bounds__(64 * kF32Waves) void k_gemm_f32_split(int m_pad, int k_pad, const int32_t *tile_cols,
+                                                                  const float *Mf, const float *in, float *out,
+                                                                  const double *col_scale, int accumulate,
+                                                                  const int8_t *add_col, int split) {
+    __shared__ __align__(16) float4 red[kF32Waves][4][64];  // [wave][4 accumulator values][lane]
+    const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = w % split;
+    const int nrb = m_pad / 32, nkc = k_pad / 32;
+    const int rb = (int)blockIdx.y * (kF32Waves / split) + w / split;  // wave-uniform
+    const int o = tile_cols[(size_t)blockIdx.x * kGemmCols + c];
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    if (rb < nrb) {
+        const int k0 = nkc * part / split, k1 = nkc * (part + 1) / split;
+        const float4 *ap = (const float4 *)Mf + (size_t)rb * nkc * 256 + lane;
+        const float4 *bp = (const float4 *)(in + (size_t)max(o, 0) * k_pad + 16 * h);
+        struct Frag {
+            float4 a[4], b[4];
+        } f[2];
+        auto load = [&](Frag &x, int kc) {
+            kc = min(kc, k1 - 1);  // past the end the last chunk again: no branch around the loads
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                x.a[i] = ap[(size_t)kc * 256 + 64 * i];
+                x.b[i] = bp[8 * kc + i];
+            }
+        };
+        auto mma = [&](const Frag &x) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float4 b = x.b[i];
+                if (o < 0) b = make_float4(0.f, 0.f, 0.f, 0.f);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.a[i].x, b.x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.a[i].y, b.y, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.a[i].z, b.z, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.a[i].w, b.w, acc, 0, 0, 0);
+            }
+        };
+        if (k0 < k1) {
+            load(f[0], k0);
+            for (int kc = k0; kc < k1; kc += 2) {
+                load(f[1], kc + 1);
+                mma(f[0]);
+                load(f[0], kc + 2);
+                if (kc + 1 < k1) mma(f[1]);
+            }
+        }
+    }
+    if (split > 1) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            red[w][j][lane] = make_float4(acc[4 * j], acc[4 * j + 1], acc[4 * j + 2], acc[4 * j + 3]);
+        __syncthreads();
+    }
+    if (rb >= nrb || o < 0) return;
+    const float sc = col_scale ? (float)col_scale[o] : 1.f;
+    const bool add = accumulate || (add_col && add_col[o]);
+    // element 4 j + e of lane l is row 8 j + 4 (l / 32) + e; the waves of a block write its j in turn
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if (j % split != part % 4 || (split == 8 && part >= 4)) continue;
+        float4 r = split > 1 ? red[w - part][j][lane] : make_float4(acc[4 * j], acc[4 * j + 1], acc[4 * j + 2], acc[4 * j + 3]);
+        for (int p = 1; p < split; ++p) {
+            const float4 x = red[w - part + p][j][lane];
+            r.x += x.x;
+            r.y += x.y;
+            r.z += x.z;
+            r.w += x.w;
+        }
+        float4 *dst = (float4 *)(out + (size_t)o * m_pad + 32 * rb + 8 * j + 4 * h);
+        r.x *= sc;
+        r.y *= sc;
+        r.z *= sc;
+        r.w *= sc;
+        if (add) {
+            const float4 old = *dst;
+            r.x += old.x;
+            r.y += old.y;
+            r.z += old.z;
+            r.w += old.w;
+        }
+        *dst = r;
+    }
+}
+
 // float64 row-major [rows][cols] -> the float32 fragment order of k_gemm_f32:
 // out[((rb * nkc + kc) * 4 + f) * 256 + 4 lane + e] = M[32 rb + lane % 32][32 kc + 16 (lane / 32) + 4 f + e]
 __global__ void k_frag_f32(const double *M, int rows, int cols, int m_pad, int k_pad, float *out) {
@@ -341,6 +437,20 @@ void dense_gemm_f32(int m_pad, int k_pad, int ntile, const int32_t *tile_cols, c
     FMM_REQUIRE(m_pad > 0 && k_pad > 0 && m_pad % 32 == 0 && k_pad % 32 == 0 && m_pad <= 512,
                 "dense_gemm_f32: unsupported size");
     const int nrb = m_pad / 32, nw = std::min(nrb, 8);  // waves per workgroup; each owns ceil(nrb / nw) row blocks
+    // Few tiles: k chunks shared by enough waves for two on each SIMD. Short
+    // products (fewer than 8 chunks) gain only with very few tiles (257 tiles,
+    // 96 x 128: 7.0 us in one workgroup a tile, 9.1-11 us split).
+    int split = 1;
+    if (k_pad >= 256 || ntile <= 64)
+        while (split < kF32Waves && (int64_t)ntile * nrb * split < 2048) split *= 2;
+    if (split > 1) {
+        const int per = kF32Waves / split;
+        hipLaunchKernelGGL(k_gemm_f32_split, dim3((unsigned)ntile, (unsigned)((nrb + per - 1) / per)),
+                           dim3(64 * kF32Waves), 0, s, m_pad, k_pad, tile_cols, M, in, out, col_scale, accumulate, add_col,
+                           split);
+        FMM_HIP(hipGetLastError());
+        return;
+    }
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3((unsigned)ntile), dim3(64 * nw), 0, s, m_pad, k_pad, tile_cols, M, in, out,
                            col_scale, accumulate, add_col);
