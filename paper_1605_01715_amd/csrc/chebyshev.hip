@@ -63,6 +63,44 @@ __device__ inline void cheb_lagrange_1d(const double *cf, double t, T *s, T *ds)
     }
 }
 
+// acc[i][r] += the terms of two staged sources at nodes (i, jy, kz): their
+// float32 terms are added, then one float64 add
+template <int N, int NRHS, bool SL, bool DL, int W, int OS, int OD, int OQ, int OM>
+__device__ inline void pair_to_nodes(const float *p0, int jy, int kz, double (&acc)[N][NRHS]) {
+    // the weights of x-node i for one source: S_x(i) A + dS_x(i) B
+    auto weights = [&](const float *p, float (&A)[NRHS], float (&B)[NRHS]) {
+        const float sy = p[OS + N + jy], sz = p[OS + 2 * N + kz];
+#pragma unroll
+        for (int r = 0; r < NRHS; ++r) {
+            A[r] = SL ? p[OQ + r] * (sy * sz) : 0.f;
+            B[r] = 0.f;
+        }
+        if (DL) {
+            const float dsy = p[OD + N + jy], dsz = p[OD + 2 * N + kz];
+#pragma unroll
+            for (int r = 0; r < NRHS; ++r) {
+                A[r] += p[OM + 3 * r + 1] * (dsy * sz) + p[OM + 3 * r + 2] * (sy * dsz);
+                B[r] = p[OM + 3 * r] * (sy * sz);
+            }
+        }
+    };
+    const float *p1 = p0 + W;
+    float A0[NRHS], B0[NRHS], A1[NRHS], B1[NRHS];
+    weights(p0, A0, B0);
+    weights(p1, A1, B1);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const float sx0 = p0[OS + i], sx1 = p1[OS + i];
+        const float dsx0 = DL ? p0[OD + i] : 0.f, dsx1 = DL ? p1[OD + i] : 0.f;
+#pragma unroll
+        for (int r = 0; r < NRHS; ++r) {
+            const float t0 = DL ? sx0 * A0[r] + dsx0 * B0[r] : sx0 * A0[r];
+            const float t1 = DL ? sx1 * A1[r] + dsx1 * B1[r] : sx1 * A1[r];
+            acc[i][r] += (double)(t0 + t1);
+        }
+    }
+}
+
 template <int N, int NRHS, bool SL, bool DL>
 __global__ __launch_bounds__(64) void k_points_to_nodes(const double *coef, const int32_t *items, const int32_t *roff,
                                                        const int32_t *rng, SurfaceGeom g, PointSrc src, float *out) {
@@ -110,41 +148,8 @@ __global__ __launch_bounds__(64) void k_points_to_nodes(const double *coef, cons
                     }
             }
             __syncthreads();
-            // the weights of x-node i for one source: S_x(i) A + dS_x(i) B
-            auto weights = [&](const float *p, float (&A)[NRHS], float (&B)[NRHS]) {
-                const float sy = p[OS + N + jy], sz = p[OS + 2 * N + kz];
-#pragma unroll
-                for (int r = 0; r < NRHS; ++r) {
-                    A[r] = SL ? p[OQ + r] * (sy * sz) : 0.f;
-                    B[r] = 0.f;
-                }
-                if (DL) {
-                    const float dsy = p[OD + N + jy], dsz = p[OD + 2 * N + kz];
-#pragma unroll
-                    for (int r = 0; r < NRHS; ++r) {
-                        A[r] += p[OM + 3 * r + 1] * (dsy * sz) + p[OM + 3 * r + 2] * (sy * dsz);
-                        B[r] = p[OM + 3 * r] * (sy * sz);
-                    }
-                }
-            };
-            for (int jj = 0; jj < cnt; jj += 2) {
-                // two sources per step: their float32 terms are added, then one float64 add
-                const float *p0 = sh + jj * W, *p1 = p0 + W;
-                float A0[NRHS], B0[NRHS], A1[NRHS], B1[NRHS];
-                weights(p0, A0, B0);
-                weights(p1, A1, B1);
-#pragma unroll
-                for (int i = 0; i < N; ++i) {
-                    const float sx0 = p0[OS + i], sx1 = p1[OS + i];
-                    const float dsx0 = DL ? p0[OD + i] : 0.f, dsx1 = DL ? p1[OD + i] : 0.f;
-#pragma unroll
-                    for (int r = 0; r < NRHS; ++r) {
-                        const float t0 = DL ? sx0 * A0[r] + dsx0 * B0[r] : sx0 * A0[r];
-                        const float t1 = DL ? sx1 * A1[r] + dsx1 * B1[r] : sx1 * A1[r];
-                        acc[i][r] += (double)(t0 + t1);
-                    }
-                }
-            }
+            for (int jj = 0; jj < cnt; jj += 2)
+                pair_to_nodes<N, NRHS, SL, DL, W, OS, OD, OQ, OM>(sh + jj * W, jy, kz, acc);
             __syncthreads();
         }
     }
@@ -153,6 +158,88 @@ __global__ __launch_bounds__(64) void k_points_to_nodes(const double *coef, cons
     for (int i = 0; i < N; ++i)
         for (int r = 0; r < NRHS; ++r)
             out[((int64_t)b * NRHS + r) * g.n_pad + (i * N + jy) * N + kz] = (float)acc[i][r];
+}
+
+// P2M where there are fewer leaves than the chip has wave slots: four waves
+// per leaf. Tiles of 64 sources are staged by all (wave c < 3 forms the
+// weights of axis c, wave 3 copies the strengths) and their pairs of sources
+// dealt to the waves, whose sums are added in LDS in a fixed order. Each pair's
+// term and the float64 accumulation are those of the kernel above.
+// Bound by latency there (one wave a leaf runs two tiles of staging and 64
+// sources in sequence); with more leaves the staging's barriers and the final
+// sums cost more than they save. Measured, one wave -> four: 224 leaves, double
+// layer, n = 8 20 -> 11.5 us; 6953 leaves 28 -> 35 us; 77,834 leaves 502 -> 634
+// us.
+template <int N, int NRHS, bool SL, bool DL>
+__global__ __launch_bounds__(256) void k_points_to_nodes4(const double *coef, const int32_t *items,
+                                                         const int32_t *roff, const int32_t *rng, SurfaceGeom g,
+                                                         PointSrc src, float *out) {
+    constexpr int OS = 0, OD = 3 * N, OQ = DL ? 6 * N : 3 * N, OM = OQ + (SL ? NRHS : 0);
+    constexpr int W = OM + (DL ? 3 * NRHS : 0), NW = 4;
+    constexpr size_t NSH = sizeof(float) * 64 * W, NRED = sizeof(double) * NW * 64 * N;
+    __shared__ __align__(16) unsigned char lds[NSH > NRED ? NSH : NRED];
+    float *sh = (float *)lds;
+    double *red = (double *)lds;  // the sums of the end reuse the records' space
+    __shared__ double cf[N * N];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b = items[blockIdx.x];
+    if (threadIdx.x < N * N) cf[threadIdx.x] = coef[threadIdx.x];
+    const double ctr = g.centre[3 * b + min(w, 2)];
+    const double ih = 1.0 / g.half[b];
+    const bool act = lane < N * N;
+    const int jy = act ? lane / N : 0, kz = act ? lane % N : 0;
+    const float *xyz = w == 0 ? src.x : w == 1 ? src.y : src.z;
+    double acc[N][NRHS];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        for (int r = 0; r < NRHS; ++r) acc[i][r] = 0.0;
+    for (int e = roff[blockIdx.x]; e < roff[blockIdx.x + 1]; ++e) {
+        const int s0 = rng[2 * e], s1 = rng[2 * e + 1];
+        for (int j0 = s0; j0 < s1; j0 += 64) {
+            const int j = j0 + lane;
+            const int cnt = min(64, s1 - j0);
+            __syncthreads();  // cf; every wave is done with the previous tile
+            float *p = sh + lane * W;
+            if (w < 3) {
+                // past the range: zero weights (the odd tail slot of the pairs below)
+                if (j < s1) {
+                    const double t = ((double)xyz[j] - ctr) * ih;
+                    cheb_lagrange_1d<N, DL>(cf, t, p + OS + w * N, p + OD + w * N);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < N; ++k) {
+                        p[OS + w * N + k] = 0.f;
+                        if (DL) p[OD + w * N + k] = 0.f;
+                    }
+                }
+            } else {
+                if (SL)
+                    for (int r = 0; r < NRHS; ++r) p[OQ + r] = j < s1 ? src.q[r * src.n + j] : 0.f;
+                if (DL)
+                    for (int r = 0; r < NRHS; ++r) {
+                        p[OM + 3 * r] = j < s1 ? (float)(src.mx[r * src.n + j] * ih) : 0.f;
+                        p[OM + 3 * r + 1] = j < s1 ? (float)(src.my[r * src.n + j] * ih) : 0.f;
+                        p[OM + 3 * r + 2] = j < s1 ? (float)(src.mz[r * src.n + j] * ih) : 0.f;
+                    }
+            }
+            __syncthreads();
+            for (int jj = 2 * w; jj < cnt; jj += 2 * NW)
+                pair_to_nodes<N, NRHS, SL, DL, W, OS, OD, OQ, OM>(sh + jj * W, jy, kz, acc);
+        }
+    }
+#pragma unroll 1
+    for (int r = 0; r < NRHS; ++r) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < N; ++i) red[(w * N + i) * 64 + lane] = acc[i][r];
+        __syncthreads();
+        if (act)
+            for (int i = w; i < N; i += NW) {
+                double v = red[i * 64 + lane];
+                for (int k = 1; k < NW; ++k) v += red[(k * N + i) * 64 + lane];
+                out[((int64_t)b * NRHS + r) * g.n_pad + i * N * N + lane] = (float)v;
+            }
+    }
 }
 
 template <int N, int NRHS, bool FIELD>
@@ -416,16 +503,17 @@ void points_to_nodes(int nrhs, bool sl, bool dl, int n, const double *coef, cons
                      hipStream_t s) {
     if (nitems <= 0) return;
     FMM_REQUIRE(g.ns == n * n * n && g.n_pad >= g.ns, "points_to_nodes: node count does not match the order");
-    dim3 gr(nitems), bl(64);
+    const bool four = nitems < 1024;  // fewer leaves than SIMDs
+    const dim3 gr(nitems), bl(four ? 256 : 64);
+    auto go = [&](auto kern1, auto kern4) {
+        hipLaunchKernelGGL((four ? kern4 : kern1), gr, bl, 0, s, coef, items, roff, rng, g, src, out);
+    };
     if (sl && dl) {
-        FMM_CHEB_SWITCH(n, nrhs, hipLaunchKernelGGL((k_points_to_nodes<N, R, true, true>), gr, bl, 0, s, coef, items,
-                                                    roff, rng, g, src, out));
+        FMM_CHEB_SWITCH(n, nrhs, go(k_points_to_nodes<N, R, true, true>, k_points_to_nodes4<N, R, true, true>));
     } else if (dl) {
-        FMM_CHEB_SWITCH(n, nrhs, hipLaunchKernelGGL((k_points_to_nodes<N, R, false, true>), gr, bl, 0, s, coef, items,
-                                                    roff, rng, g, src, out));
+        FMM_CHEB_SWITCH(n, nrhs, go(k_points_to_nodes<N, R, false, true>, k_points_to_nodes4<N, R, false, true>));
     } else {
-        FMM_CHEB_SWITCH(n, nrhs, hipLaunchKernelGGL((k_points_to_nodes<N, R, true, false>), gr, bl, 0, s, coef, items,
-                                                    roff, rng, g, src, out));
+        FMM_CHEB_SWITCH(n, nrhs, go(k_points_to_nodes<N, R, true, false>, k_points_to_nodes4<N, R, true, false>));
     }
     FMM_HIP(hipGetLastError());
 }
