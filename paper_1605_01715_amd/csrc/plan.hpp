@@ -28,6 +28,19 @@ struct GemmJob {
 
 enum Stage { ST_P2M = 0, ST_M2M, ST_P2L, ST_M2L, ST_L2L, ST_C2E, ST_EVAL, ST_COUNT };
 
+// Pinned host memory that a solve's kernels write their coefficients to (a few
+// KB, made by the plan's first solve and kept with the plan).
+struct PinnedBuf {
+    double *p = nullptr;
+    size_t n = 0;
+    PinnedBuf() = default;
+    PinnedBuf(const PinnedBuf &) = delete;
+    PinnedBuf &operator=(const PinnedBuf &) = delete;
+    ~PinnedBuf() { release(); }
+    double *get(size_t count);  // at least `count` doubles
+    void release();
+};
+
 struct Plan {
     Arena mem;  // every buffer of the plan (destroyed last)
     fmm_options opt{};
@@ -50,6 +63,7 @@ struct Plan {
     DBuf<double> col_iscale;                // 1 / half-width per vector index (Chebyshev M2L expansion)
     DBuf<int8_t> expand_add;                // per vector index: 1 where P2L writes the node values (Chebyshev expansion adds there, writes elsewhere)
     DBuf<float> trg_nrm_user;               // [n_trg][3] target normals, caller's order
+    PinnedBuf solve_host;
 
     DBuf<int32_t> p2m_items, p2m_roff, p2m_rng;
     int n_p2m = 0;
