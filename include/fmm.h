@@ -203,8 +203,9 @@ typedef struct {
  * Restarted GMRES(restart) on the operator above (Sec. III, matrix-free; the
  * paper's tolerance is 1e-5, Sec. IV.B). Orthogonalisation (classical
  * Gram-Schmidt twice) and residual norms are float64 on the device; one
- * fmm_apply and one wait for the step's coefficients per iteration. restart is 1..500; the Krylov basis takes (restart + 1) n
- * float64 of device memory, taken per call.
+ * fmm_apply and one wait for the step's coefficients per iteration. restart is
+ * 1..500; the Krylov basis takes (restart + 1) n float64 of device memory,
+ * taken per call.
  *   b        device double [n]    right-hand side
  *   x        device double [n]    in: initial guess, out: solution (best iterate)
  *   iters    host int             iterations done

@@ -183,7 +183,8 @@ void finish_plan(fmm::Plan &P, const fmm_options *opt, const float *trg_nrm, hip
     P.r = P.ops->r;
     P.r_pad = P.ops->r_pad;
     const size_t nvec = (size_t)P.t.nb * P.nrhs;
-    P.ut.alloc(nvec * P.r_pad);
+    // (the Chebyshev form's split arithmetics have their M2L input in ut_bf only)
+    if (!P.cheb || !P.m2l_form) P.ut.alloc(nvec * P.r_pad);
     P.dt.alloc(nvec * P.r_pad);
     if (!P.cheb) P.chk.alloc(nvec * P.n_pad);
     if (P.m2l_form) P.ut_bf.alloc(m2l_split_vecs_elems(P.r_pad, (int64_t)nvec, m2l_form_parts(P.m2l_form)));
@@ -197,7 +198,7 @@ void finish_plan(fmm::Plan &P, const fmm_options *opt, const float *trg_nrm, hip
     }
     // zero once: padding entries are never written, vectors of boxes
     // a stage skips stay zero
-    for (DBuf<float> *b : {&P.ut, &P.chk, &P.phi_u, &P.phi_d})
+    for (DBuf<float> *b : {&P.ut, &P.dt, &P.chk, &P.phi_u, &P.phi_d})
         if (b->n) FMM_HIP(hipMemsetAsync(b->p, 0, b->bytes(), s));
     const size_t nsv = (size_t)P.nrhs * P.t.n_src;
     if (P.sl) P.q_sorted.alloc(nsv);

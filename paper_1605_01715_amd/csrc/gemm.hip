@@ -27,6 +27,8 @@
 // 1092 -> 754 us and on a 4M cloud (order 8) 9.07 -> 8.80 ms.
 #include "gemm.hpp"
 
+#include "bf16.hpp"
+
 #include <algorithm>
 
 namespace fmm {
@@ -205,10 +207,31 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kF32Slice = 128;            // k staged per slice
 constexpr int kF32BStr = kF32Slice + 4;   // floats per column in LDS
 
+// The four rows k = row .. row + 3 (a multiple of 4) of vector o, split into
+// np parts: the M2L's input straight from the basis change, without a float32
+// copy of it in between.
+__device__ inline void store_split(uint16_t *out_bf, int np, int m_pad, int o, int row, float4 r) {
+    typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
+    const float v[4] = {r.x, r.y, r.z, r.w};
+    u16x4 h, m, l;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        uint16_t a, b, c;
+        split3(v[e], a, b, c);
+        h[e] = a;
+        m[e] = b;
+        l[e] = c;
+    }
+    uint16_t *p = out_bf + o * vec_bf_stride(m_pad, np) + (row / 32) * np * 32 + row % 32;
+    *(u16x4 *)p = h;
+    *(u16x4 *)(p + 32) = m;
+    if (np == 3) *(u16x4 *)(p + 64) = l;
+}
+
 template <int MAXRB>
 __global__ __launch_bounds__(512) void k_gemm_f32(int m_pad, int k_pad, const int32_t *tile_cols, const float *Mf,
                                                   const float *in, float *out, const double *col_scale,
-                                                  int accumulate, const int8_t *add_col) {
+                                                  int accumulate, const int8_t *add_col, uint16_t *out_bf, int np) {
     __shared__ __align__(16) float Bs[kGemmCols * kF32BStr];
     __shared__ int32_t cols[kGemmCols];
     const int t = threadIdx.x, lane = t & 63, c = lane & 31, h = lane >> 5;
@@ -286,6 +309,10 @@ __global__ __launch_bounds__(512) void k_gemm_f32(int m_pad, int k_pad, const in
         for (int v4 = 0; v4 < 4; ++v4) {
             float4 r = make_float4(acc[i][4 * v4] * sc, acc[i][4 * v4 + 1] * sc, acc[i][4 * v4 + 2] * sc,
                                    acc[i][4 * v4 + 3] * sc);
+            if (out_bf) {
+                store_split(out_bf, np, m_pad, o, (w + nw * i) * 32 + 4 * h + 8 * v4, r);
+                continue;
+            }
             float4 *dst = (float4 *)(op + 8 * v4);
             if (add) {
                 const float4 old = *dst;
@@ -312,7 +339,8 @@ constexpr int kF32Waves = 8;
 __global__ __launch_bounds__(64 * kF32Waves) void k_gemm_f32_split(int m_pad, int k_pad, const int32_t *tile_cols,
                                                                   const float *Mf, const float *in, float *out,
                                                                   const double *col_scale, int accumulate,
-                                                                  const int8_t *add_col, int split) {
+                                                                  const int8_t *add_col, uint16_t *out_bf, int np,
+                                                                  int split) {
     __shared__ __align__(16) float4 red[kF32Waves][4][64];  // [wave][4 accumulator values][lane]
     const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = w % split;
@@ -384,6 +412,10 @@ __global__ __launch_bounds__(64 * kF32Waves) void k_gemm_f32_split(int m_pad, in
         r.y *= sc;
         r.z *= sc;
         r.w *= sc;
+        if (out_bf) {
+            store_split(out_bf, np, m_pad, o, 32 * rb + 8 * j + 4 * h, r);
+            continue;
+        }
         if (add) {
             const float4 old = *dst;
             r.x += old.x;
@@ -432,10 +464,12 @@ void box_gemm_f64(const GemmLaunch &a, hipStream_t s) {
 }
 
 void dense_gemm_f32(int m_pad, int k_pad, int ntile, const int32_t *tile_cols, const float *M, const float *in,
-                    float *out, const double *col_scale, int accumulate, hipStream_t s, const int8_t *add_col) {
+                    float *out, const double *col_scale, int accumulate, hipStream_t s, const int8_t *add_col,
+                    uint16_t *out_bf, int np) {
     if (ntile <= 0) return;
     FMM_REQUIRE(m_pad > 0 && k_pad > 0 && m_pad % 32 == 0 && k_pad % 32 == 0 && m_pad <= 512,
                 "dense_gemm_f32: unsupported size");
+    FMM_REQUIRE(!out_bf || np == 2 || np == 3, "dense_gemm_f32: 2 or 3 bfloat16 parts");
     const int nrb = m_pad / 32, nw = std::min(nrb, 8);  // waves per workgroup; each owns ceil(nrb / nw) row blocks
     // Few tiles: k chunks shared by enough waves for two on each SIMD. Short
     // products (fewer than 8 chunks) gain only with very few tiles (257 tiles,
@@ -447,13 +481,13 @@ void dense_gemm_f32(int m_pad, int k_pad, int ntile, const int32_t *tile_cols, c
         const int per = kF32Waves / split;
         hipLaunchKernelGGL(k_gemm_f32_split, dim3((unsigned)ntile, (unsigned)((nrb + per - 1) / per)),
                            dim3(64 * kF32Waves), 0, s, m_pad, k_pad, tile_cols, M, in, out, col_scale, accumulate, add_col,
-                           split);
+                           out_bf, np, split);
         FMM_HIP(hipGetLastError());
         return;
     }
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3((unsigned)ntile), dim3(64 * nw), 0, s, m_pad, k_pad, tile_cols, M, in, out,
-                           col_scale, accumulate, add_col);
+                           col_scale, accumulate, add_col, out_bf, np);
     };
     if (nrb <= 8)
         go(k_gemm_f32<1>);

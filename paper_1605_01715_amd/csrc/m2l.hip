@@ -46,6 +46,8 @@
 
 #include "m2l.hpp"
 
+#include "bf16.hpp"
+
 namespace fmm {
 
 namespace {
@@ -59,30 +61,13 @@ typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 constexpr int kCols = 128;     // 4 column blocks of 32
 constexpr int KC = 32;         // k per step
 
-// float32 -> bfloat16, round to nearest even (finite inputs)
-__device__ inline uint16_t f2bf(float x) {
-    uint32_t u = __float_as_uint(x);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-__device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-// x = h + m + l up to 2^-24 |x| (each residual is exact in float32); the
-// two-part split is h and m (x = h + m up to 2^-16 |x|)
-__device__ inline void split3(float x, uint16_t &h, uint16_t &m, uint16_t &l) {
-    h = f2bf(x);
-    float r1 = x - bf2f(h);
-    m = f2bf(r1);
-    l = f2bf(r1 - bf2f(m));
-}
-
 // One A chunk (r_pad rows x 32 k) in LDS and in the global image, fragment order:
 //   BF16 (32x32x16): part p (of NP = 3 or 2), row block rb, k-half h (16 k each), lane, 8 slots;
 //                    element (row, k) -> lane = row % 32 + 32 * ((k % 16) / 8), slot = k % 8
 //   FP32 (32x32x2):  row block rb, lane, 16 slots;
 //                    element (row, k) -> lane = row % 32 + 32 * (k / 16), slot = k % 16
-// Split-BF16 source vector layout: per vector, per 32-k chunk, NP parts of 32
-// bfloat16 (64 NP bytes); float32 vectors are plain rows of r_pad values.
-__host__ __device__ constexpr int64_t vec_bf_stride(int r_pad, int np) { return np * (int64_t)r_pad; }
+// Split-BF16 source vectors: the layout of bf16.hpp; float32 vectors are plain
+// rows of r_pad values.
 
 // M2L arithmetic: 0 float32; 6, 4, 3 the split-BF16 products (parts: 3, 2, 2)
 __host__ __device__ constexpr int form_parts(int form) { return form == 6 ? 3 : 2; }
@@ -356,7 +341,8 @@ __global__ __launch_bounds__(NW * 64, 2) void k_m2l(M2LLaunch a) {
 #pragma unroll
             for (int v4 = 0; v4 < 4; ++v4) {
                 f32x4 *op = (f32x4 *)(a.out + (size_t)outv * RP + rb * 32 + 8 * v4 + 4 * hf);
-                f32x4 cur = *op;
+                f32x4 cur = {0.f, 0.f, 0.f, 0.f};
+                if (a.accumulate) cur = *op;
                 cur[0] += acc[i][4 * v4];
                 cur[1] += acc[i][4 * v4 + 1];
                 cur[2] += acc[i][4 * v4 + 2];
@@ -367,12 +353,14 @@ __global__ __launch_bounds__(NW * 64, 2) void k_m2l(M2LLaunch a) {
     }
 }
 
+// (These and the kernel above add to out, or with accumulate = 0 write it.)
 // Cut tiles: out[cols[c]] += partial[slot0] + partial[slot0 + 1] + ... (in
 // piece order, so the result does not depend on which piece ran first).
 // Block (tile, g) adds columns 16 g .. 16 g + 15, four values per thread.
 constexpr int kRedCols = 16;
 __global__ __launch_bounds__(256) void k_m2l_reduce(int r_pad, int ncol, const int32_t *cols, const int32_t *slot0,
-                                                    const int32_t *kpieces, const float *partial, float *out) {
+                                                    const int32_t *kpieces, const float *partial, float *out,
+                                                    int accumulate) {
     const int tl = blockIdx.x;
     const int k = kpieces[tl];
     const size_t per = (size_t)ncol * r_pad;  // floats per slot
@@ -385,7 +373,7 @@ __global__ __launch_bounds__(256) void k_m2l_reduce(int r_pad, int ncol, const i
         f32x4 sum = *(const f32x4 *)p;
         for (int q = 1; q < k; ++q) sum += *(const f32x4 *)(p + q * per);
         f32x4 *o = (f32x4 *)(out + (size_t)v * r_pad + r4);
-        *o = *o + sum;
+        *o = accumulate ? *o + sum : sum;
     }
 }
 
@@ -400,7 +388,8 @@ __global__ __launch_bounds__(256) void k_m2l_reduce(int r_pad, int ncol, const i
 // 100,070 at 192 552 -> 536 us.
 constexpr int kGatherThreads = 256;
 __global__ __launch_bounds__(kGatherThreads) void k_m2l_gather(int r_pad, const int32_t *targets, const int32_t *off,
-                                                              const int32_t *rows, const float *partial, float *out) {
+                                                              const int32_t *rows, const float *partial, float *out,
+                                                              int accumulate) {
     __shared__ int32_t idx[kGatherThreads];
     __shared__ f32x4 red[kGatherThreads];
     const int t = threadIdx.x, q4 = r_pad / 4, ng = kGatherThreads / q4;
@@ -426,7 +415,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_m2l_gather(int r_pad, const 
     if (grp > 0) return;
     for (int g = 1; g < ng; ++g) sum += red[g * q4 + t];
     f32x4 *o = (f32x4 *)(out + (size_t)v * r_pad + c);
-    *o = *o + sum;
+    *o = accumulate ? *o + sum : sum;
 }
 
 // Matrices [ndir][r_pad][r_pad] float32 -> split-BF16 chunks (np = 3 or 2
@@ -621,19 +610,20 @@ int m2l_blocks_per_cu(int form, int r_pad) {
 }
 
 void m2l_reduce(int r_pad, int ntile, int ncol, const int32_t *cols, const int32_t *slot0, const int32_t *kpieces,
-                const float *partial, float *out, hipStream_t s) {
+                const float *partial, float *out, bool accumulate, hipStream_t s) {
     if (ntile <= 0) return;
     FMM_REQUIRE(ncol % kRedCols == 0 && r_pad % 4 == 0, "m2l_reduce: unsupported tile shape");
     hipLaunchKernelGGL(k_m2l_reduce, dim3(ntile, ncol / kRedCols), dim3(256), 0, s, r_pad, ncol, cols, slot0, kpieces,
-                       partial, out);
+                       partial, out, accumulate ? 1 : 0);
     FMM_HIP(hipGetLastError());
 }
 
 void m2l_gather(int r_pad, int n, const int32_t *targets, const int32_t *off, const int32_t *rows,
-                const float *partial, float *out, hipStream_t s) {
+                const float *partial, float *out, bool accumulate, hipStream_t s) {
     if (n <= 0) return;
     FMM_REQUIRE(m2l_supported(r_pad), "m2l_gather: unsupported state size");
-    hipLaunchKernelGGL(k_m2l_gather, dim3(n), dim3(kGatherThreads), 0, s, r_pad, targets, off, rows, partial, out);
+    hipLaunchKernelGGL(k_m2l_gather, dim3(n), dim3(kGatherThreads), 0, s, r_pad, targets, off, rows, partial, out,
+                       accumulate ? 1 : 0);
     FMM_HIP(hipGetLastError());
 }
 

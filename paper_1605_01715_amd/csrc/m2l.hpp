@@ -30,6 +30,7 @@ struct M2LLaunch {
     const int32_t *piece_slot = nullptr;  // per tile: -1, or the slot of partial it writes instead of adding to out
     float *partial = nullptr;             // [slot][ncol][r_pad]
     float *out = nullptr;
+    int accumulate = 1;  // add to out; 0: write it (each vector belongs to one tile)
 };
 
 int m2l_ncol(int r_pad);
@@ -39,10 +40,11 @@ int m2l_form_parts(int form);                  // bfloat16 parts per value of a 
 int m2l_blocks_per_cu(int form, int r_pad);    // workgroups of the kernel that fit on one CU
 // cut tiles: out[cols[t][c]] += sum over q < kpieces[t] of partial[slot0[t] + q][c] (q in order)
 void m2l_reduce(int r_pad, int ntile, int ncol, const int32_t *cols, const int32_t *slot0, const int32_t *kpieces,
-                const float *partial, float *out, hipStream_t s);
-// pair tiles: out[targets[t]] += sum over e in [off[t], off[t+1]) of partial row rows[e] (in order)
+                const float *partial, float *out, bool accumulate, hipStream_t s);
+// pair tiles: out[targets[t]] += sum over e in [off[t], off[t+1]) of partial row rows[e] (in a fixed order);
+// accumulate = false: = instead of += (both)
 void m2l_gather(int r_pad, int n, const int32_t *targets, const int32_t *off, const int32_t *rows,
-                const float *partial, float *out, hipStream_t s);
+                const float *partial, float *out, bool accumulate, hipStream_t s);
 bool m2l_supported(int r_pad);  // any multiple of 32 up to 512
 void m2l_run(int form, const M2LLaunch &a, hipStream_t s);
 

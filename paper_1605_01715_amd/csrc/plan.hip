@@ -1136,16 +1136,14 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
                            t.n_src, nrhs, q, mu, t.snx.p, t.sny.p, t.snz.p, P.q_sorted.p, P.mx.p, P.my.p, P.mz.p);
     }
     FMM_HIP(hipGetLastError());
-    // the M2L output accumulates (translation, reduction, gather and, in the
-    // surface form, the P2L projection): cleared once per apply, in the
-    // Chebyshev form only after the fork, where it waits behind the
-    // evaluation's workgroups instead of ahead of P2M
-    auto clear_dt = [&]() {
-        if (!P.dt.n) return;
+    // The surface form's M2L output collects the P2L projection, the translation
+    // and, in place, L2L: cleared once per apply. In the Chebyshev form each
+    // vector is written by the one tile (or reduction, or gather) that owns it,
+    // and the others keep the zeros of the setup.
+    if (!P.cheb && P.dt.n) {
         hipLaunchKernelGGL(k_zero, dim3(grid_for((int64_t)P.dt.n, kBlock)), dim3(kBlock), 0, s, P.dt.p, (int64_t)P.dt.n);
         FMM_HIP(hipGetLastError());
-    };
-    if (!P.cheb) clear_dt();
+    }
     const int np = P.n_pad, rp = P.r_pad;
 
     PointSrc src;
@@ -1184,12 +1182,14 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
         m.piece_slot = P.m2l_slot.p;
         m.partial = P.m2l_partial.p;
         m.out = P.dt.p;
+        m.accumulate = P.cheb ? 0 : 1;
         m2l_run(P.m2l_form, m, s);
         if (P.m2l_nsplit > 0)
             m2l_reduce(rp, P.m2l_nsplit, P.m2l_ncol, P.m2l_red_cols.p, P.m2l_red_slot0.p, P.m2l_red_k.p, P.m2l_partial.p,
-                       P.dt.p, s);
+                       P.dt.p, !P.cheb, s);
         if (P.m2l_ngather > 0)
-            m2l_gather(rp, P.m2l_ngather, P.m2l_gt.p, P.m2l_goff.p, P.m2l_gidx.p, P.m2l_partial.p, P.dt.p, s);
+            m2l_gather(rp, P.m2l_ngather, P.m2l_gt.p, P.m2l_goff.p, P.m2l_gidx.p, P.m2l_partial.p, P.dt.p, !P.cheb,
+                       s);
     };
 
     EvalArgs e;
@@ -1261,9 +1261,10 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
         mark(ST_M2M);
         for (auto &j : P.cheb_m2m)
             cheb_tensor(nrhs, op.p, false, op.cheb_s1.p, j.n, j.dst.p, j.src.p, nullptr, P.phi_u.p, P.phi_u.p, np, s);
-        // the upward pass ends with the weights in the M2L basis
+        // the upward pass ends with the weights in the M2L basis, for the split
+        // forms already in their bfloat16 parts
         dense_gemm_f32(rp, np, P.cheb_compress.ntile, P.cheb_compress.cols.p, op.pv_f32.p, P.phi_u.p, P.ut.p,
-                       nullptr, 0, s);
+                       nullptr, 0, s, nullptr, P.m2l_form ? P.ut_bf.p : nullptr, m2l_form_parts(P.m2l_form));
         // side stream, second: the leaf evaluation, beside M2L and L2L
         FMM_HIP(hipEventRecord(P.fork, s));
         FMM_HIP(hipStreamWaitEvent(P.side, P.fork, 0));
@@ -1272,12 +1273,6 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
         if (ts) FMM_HIP(hipEventRecord(ts->side[3], P.side));
         FMM_HIP(hipEventRecord(P.join, P.side));
         mark(ST_P2L);  // (P2L runs on the side stream; timed there)
-        // the clearing of the M2L output and the split of its input queue
-        // behind the evaluation's workgroups; they stay out of the M2L
-        // stage, which times the translation kernel, the reduction and the
-        // gather
-        clear_dt();
-        split_m2l_input();
         mark(ST_M2L);
         run_m2l();
         mark(ST_L2L);
