@@ -441,7 +441,7 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         // partners (points on surfaces), a tile runs every direction for
         // only a fraction of its columns (fill 0.2-0.3 on the sphere
         // workloads). The (direction, target) pairs of tiles with fill below
-        // kPairFill are regrouped by direction into tiles of one direction
+        // pair_fill are regrouped by direction into tiles of one direction
         // whose columns are pairs, all live; each writes its
         // products to a partial-sum slot, and a gather adds each target's
         // partials in direction order. Costs: a tile does 6 steps per
@@ -450,8 +450,86 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         // 4M-point cloud's apply is 4% faster (its tiles between the two
         // fills are cheaper as tiles), and the sphere workloads, whose sparse
         // tiles sit near fill 0.2-0.3, are unchanged.
+        // A float32 step costs several times a bfloat16 one for the same
+        // partials, so there the line lies at 0.65 (300,000-point cloud, order
+        // 6: 1552 us at 0.45, 1455 at 0.55, 1448 at 0.65, 1461 at 0.8; 2M
+        // points, Chebyshev: 5677 us at 0.45, 5283 at 0.55, 5201 at 0.65),
+        // except with matrices below 96 rows, where the partials are most of
+        // a step (order 4, 400,000 points: 676 us at 0.45, 747 at 0.65), where
+        // the partials would pass 4 GiB, and where the dispatch would not end
+        // 5% sooner: in a 100,000-point cube, order 6, the 16 full tiles bound
+        // it whatever becomes of the other 24 (602 us, 703 at 0.65).
         lap("m2l direction lists");
-        constexpr double kPairFill = 0.45;
+        // The dispatch of tiles with nd directions on XCD oct, k pieces each:
+        // the longest XCD's makespan in steps, with a cost of 2 directions per
+        // piece of a cut tile
+        const int slots = 32 * m2l_blocks_per_cu(P.m2l_form, P.r_pad);  // concurrent workgroups per XCD
+        auto makespan = [&](const std::vector<int> &nd, const std::vector<int> &oct, int k) {
+            double worst = 0.0;
+#pragma omp parallel for schedule(dynamic, 1) reduction(max : worst)
+            for (int x = 0; x < 8; ++x) {
+                std::vector<double> w;
+                for (size_t tl = 0; tl < nd.size(); ++tl) {
+                    if (oct[tl] != x) continue;
+                    const int kk = std::min(k, nd[tl]);
+                    for (int q = 0; q < kk; ++q) w.push_back((double)nd[tl] / kk + (kk > 1 ? 2.0 : 0.0));
+                }
+                std::sort(w.begin(), w.end(), std::greater<double>());
+                std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
+                for (int q = 0; q < slots; ++q) busy.push(0.0);
+                double end = 0.0;
+                for (double v : w) {
+                    const double t0 = busy.top();
+                    busy.pop();
+                    busy.push(t0 + v);
+                    end = std::max(end, t0 + v);
+                }
+                worst = std::max(worst, end);
+            }
+            return worst;
+        };
+        // the best of 1 to 6 pieces a tile, and its makespan
+        auto best_pieces = [&](const std::vector<int> &nd, const std::vector<int> &oct) {
+            std::pair<int, double> best{1, makespan(nd, oct, 1)};
+            for (int k = 2; k <= 6; ++k) {
+                const double m = makespan(nd, oct, k);
+                if (m < best.second * 0.995) best = {k, m};
+            }
+            return best;
+        };
+        double pair_fill = 0.45;
+        std::vector<int64_t> tlive(ntile, 0);
+        for (int tl = 0; tl < ntile; ++tl)
+            for (int d = 0; d < kNumDirs; ++d) tlive[tl] += tcnt[(size_t)tl * kNumDirs + d];
+        auto sparse_at = [&](int tl, double fill) {
+            const int64_t n = toff[tl + 1] - toff[tl];
+            return n > 0 && (double)tlive[tl] < fill * (double)n * nc;
+        };
+        if (P.m2l_form == 0 && P.r_pad >= 96) {
+            // the makespan with the tiles below `fill` as pair tiles, and the pair tiles' count
+            auto span_at = [&](double fill, int64_t &npair) {
+                std::vector<int> nd, oct;
+                std::vector<int64_t> pairs(kNumDirs, 0);
+                for (int tl = 0; tl < ntile; ++tl) {
+                    if (sparse_at(tl, fill)) {
+                        for (int d = 0; d < kNumDirs; ++d) pairs[d] += tcnt[(size_t)tl * kNumDirs + d];
+                    } else {
+                        nd.push_back((int)(toff[tl + 1] - toff[tl]));
+                        oct.push_back(tile_oct[tl]);
+                    }
+                }
+                npair = 0;
+                for (int d = 0; d < kNumDirs; ++d) npair += (pairs[d] + nc - 1) / nc;
+                for (int64_t i = 0; i < npair; ++i) {
+                    nd.push_back(1);
+                    oct.push_back((int)(i % 8));
+                }
+                return best_pieces(nd, oct).second;
+            };
+            int64_t n45, n65;
+            const double s45 = span_at(0.45, n45), s65 = span_at(0.65, n65);
+            if (s65 < 0.95 * s45 && n65 * nc * P.r_pad * (int64_t)sizeof(float) <= (int64_t)4 << 30) pair_fill = 0.65;
+        }
         std::vector<uint8_t> pair_tile(ntile, 0);
         {
             // the columns of the sparse tiles
@@ -459,10 +537,7 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             std::vector<uint8_t> keep(ntile, 1);
             bool moved = false;
             for (int tl = 0; tl < ntile; ++tl) {
-                const int64_t n = toff[tl + 1] - toff[tl];
-                int64_t live = 0;
-                for (int d = 0; d < kNumDirs; ++d) live += tcnt[(size_t)tl * kNumDirs + d];
-                if (n == 0 || (double)live >= kPairFill * (double)n * nc) continue;
+                if (!sparse_at(tl, pair_fill)) continue;
                 keep[tl] = 0;
                 moved = true;
                 for (int c = 0; c < nc; ++c) {
@@ -561,45 +636,12 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         // workgroup slot) for k = 1..6 unless the options force k. Pieces of a cut tile write partial
         // sums, added to the output in piece order by a second kernel.
         {
-            const int slots = 32 * m2l_blocks_per_cu(P.m2l_form, P.r_pad);  // concurrent workgroups per XCD
             auto ndir = [&](int tl) { return (int)(toff[tl + 1] - toff[tl]); };
-            // makespan of one XCD in steps, with a cost of 2 directions per piece of a cut tile
-            std::vector<std::vector<int>> tiles_of(8);
-            for (int tl = 0; tl < ntile; ++tl) tiles_of[tile_oct[tl]].push_back(tl);
-            auto makespan = [&](int k) {
-                double worst = 0.0;
-#pragma omp parallel for schedule(dynamic, 1) reduction(max : worst)
-                for (int x = 0; x < 8; ++x) {
-                    std::vector<double> w;
-                    for (int tl : tiles_of[x]) {
-                        const int kk = std::min(k, ndir(tl));
-                        for (int q = 0; q < kk; ++q) w.push_back((double)ndir(tl) / kk + (kk > 1 ? 2.0 : 0.0));
-                    }
-                    std::sort(w.begin(), w.end(), std::greater<double>());
-                    std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
-                    for (int q = 0; q < slots; ++q) busy.push(0.0);
-                    double end = 0.0;
-                    for (double v : w) {
-                        const double t0 = busy.top();
-                        busy.pop();
-                        busy.push(t0 + v);
-                        end = std::max(end, t0 + v);
-                    }
-                    worst = std::max(worst, end);
-                }
-                return worst;
-            };
             int kbest = P.opt.m2l_pieces;  // forced, or 0: simulated
             if (kbest == 0) {
-                kbest = 1;
-                double best = makespan(1);
-                for (int k = 2; k <= 6; ++k) {
-                    const double m = makespan(k);
-                    if (m < best * 0.995) {
-                        best = m;
-                        kbest = k;
-                    }
-                }
+                std::vector<int> nd(ntile);
+                for (int tl = 0; tl < ntile; ++tl) nd[tl] = ndir(tl);
+                kbest = best_pieces(nd, tile_oct).first;
             }
             lap("m2l pair tiles and piece model");
             P.m2l_pieces_per_tile = kbest;
