@@ -100,6 +100,13 @@ __device__ inline void copy_to_lds(const void *src, void *dst) {
 // barriers. Either way every wave reads the matrix chunk rows it multiplies
 // (4 reads of the chunk per step); with 4 waves the source chunk is read
 // once per column block instead of twice (one row half each).
+//
+// LEAN (float32, up to 192 rows): operands are read four k at a time, so that
+// 80 registers hold a wave and three workgroups, not two, share a CU. A tile
+// of one direction is half waiting (its lists, the first copies, its stores):
+// 640 of them, 160 rows, 4096 points: apply 140 -> 134 us; 2400 of 96 rows,
+// 80,640 points on triangles: 221 -> 210 with the evaluation after them. The
+// products of an accumulator and their order are the same.
 template <int NRB, int FORM, int NW>
 struct Shape {
     static_assert(NW == 8 || NW == 4, "8 or 4 waves");
@@ -124,8 +131,8 @@ struct Shape {
     static_assert(kCols * SPC % 64 == 0, "B slots must fill whole copies");
 };
 
-template <int NRB, int FORM, int NW>
-__global__ __launch_bounds__(NW * 64, 2) void k_m2l(M2LLaunch a) {
+template <int NRB, int FORM, int NW, bool LEAN>
+__global__ __launch_bounds__(NW * 64, LEAN ? 6 : 2) void k_m2l(M2LLaunch a) {
     using S = Shape<NRB, FORM, NW>;
     constexpr bool BF16 = S::BF16;
     constexpr int NP = S::NP;
@@ -158,23 +165,17 @@ __global__ __launch_bounds__(NW * 64, 2) void k_m2l(M2LLaunch a) {
     // B copies: copy i = w + NW j fills LDS slots 64 i .. 64 i + 63; slot q is
     // piece q % SPC of column q / SPC (piece PPC is the pad slot). Columns
     // without a source for the direction, and pad slots, copy zeros.
-    int bcol[JB], bpiece[JB];
-#pragma unroll
-    for (int j = 0; j < JB; ++j) {
-        const int q = (w + NW * j) * 64 + lane;
-        bcol[j] = min(q / SPC, kCols - 1);
-        bpiece[j] = q % SPC;
-    }
-    int cur_sv[JB], nxt_sv[JB], cur_own = -1, nxt_own = -1;
+    auto bcol = [&](int j) { return min(((w + NW * j) * 64 + lane) / SPC, kCols - 1); };
+    auto bpiece = [&](int j) { return ((w + NW * j) * 64 + lane) % SPC; };
+    int cur_sv[JB], cur_own = -1;  // sources of the next step to be copied
     auto fetch_src = [&](int e, int (&sv)[JB], int &own) {
         const int64_t row = (toff + e) * kCols;
 #pragma unroll
-        for (int j = 0; j < JB; ++j) sv[j] = a.term_src[row + bcol[j]];
+        for (int j = 0; j < JB; ++j) sv[j] = a.term_src[row + bcol(j)];
         own = a.term_src[row + my_col];
     };
     if (nact > 0) {
         fetch_src(0, cur_sv, cur_own);
-        fetch_src(nact > 1 ? 1 : 0, nxt_sv, nxt_own);
     }
     __syncthreads();  // s_dir
 
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_m2l(M2LLaunch a) {
         for (int j = 0; j < JB; ++j) {
             const int i = w + NW * j;
             if (NIB % NW != 0 && i >= NIB) continue;
-            const int pc = bpiece[j];
+            const int pc = bpiece(j);
             const unsigned char *src;
             if (cur_sv[j] < 0 || pc == PPC)
                 src = (const unsigned char *)a.zero + 16 * (pc % PPC);
@@ -218,10 +219,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_m2l(M2LLaunch a) {
             e_ld = 0;
             ++st_ld;
         }
-#pragma unroll
-        for (int j = 0; j < JB; ++j) cur_sv[j] = nxt_sv[j];
-        cur_own = nxt_own;
-        fetch_src(e_ld + 1 < nact ? e_ld + 1 : 0, nxt_sv, nxt_own);
+        fetch_src(e_ld, cur_sv, cur_own);
     };
 
     // Operand fragments of one step. The two buffers are distinct LDS
@@ -308,12 +306,29 @@ __global__ __launch_bounds__(NW * 64, 2) void k_m2l(M2LLaunch a) {
             __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
             __syncthreads();                      // step s is in LDS
             if (live_s) {
-                read_b(0);
+                if constexpr (LEAN) {
+                    const float *pa = (const float *)sA[0] + lane * 16, *pb = (const float *)(sB[0] + my_col * BSTR + 64 * hf);
 #pragma unroll
-                for (int i = 0; i < RBH; ++i) {
-                    if (i >= nrb) continue;
-                    read_a(0, rb0 + i, fa);
-                    mfma_row(i, fa);
+                    for (int f = 0; f < 4; ++f) {
+                        const f32x4 b4 = *(const f32x4 *)(pb + 4 * f);
+#pragma unroll
+                        for (int i = 0; i < RBH; ++i) {
+                            if (i >= nrb) continue;
+                            const f32x4 a4 = *(const f32x4 *)(pa + (rb0 + i) * 1024 + 4 * f);
+                            f32x16 c = acc[i];
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a4[q], b4[q], c, 0, 0, 0);
+                            acc[i] = c;
+                        }
+                    }
+                } else {
+                    read_b(0);
+#pragma unroll
+                    for (int i = 0; i < RBH; ++i) {
+                        if (i >= nrb) continue;
+                        read_a(0, rb0 + i, fa);
+                        mfma_row(i, fa);
+                    }
                 }
             }
             __syncthreads();  // every wave is done with the buffer
@@ -510,22 +525,36 @@ constexpr int waves_for() {
     return (FORM != 0 && NRB <= 6) ? 4 : 8;
 }
 
+// float32 up to 192 rows: the accumulators of three workgroups fit on a CU
+template <int NRB, int FORM>
+constexpr bool can_be_lean() {
+    return FORM == 0 && NRB <= 6;
+}
+
 template <int NRB, int FORM>
 void launch(const M2LLaunch &a, hipStream_t s) {
     constexpr int NW = waves_for<NRB, FORM>();
     using S = Shape<NRB, FORM, NW>;
     static_assert(S::NBUF == 2 || S::LDS2 / 2 <= 160 * 1024, "chunks do not fit in LDS");
-    hipLaunchKernelGGL((k_m2l<NRB, FORM, NW>), dim3(a.ntile), dim3(NW * 64), 0, s, a);
+    if constexpr (can_be_lean<NRB, FORM>())
+        if (a.lean) {
+            hipLaunchKernelGGL((k_m2l<NRB, FORM, NW, true>), dim3(a.ntile), dim3(NW * 64), 0, s, a);
+            FMM_HIP(hipGetLastError());
+            return;
+        }
+    hipLaunchKernelGGL((k_m2l<NRB, FORM, NW, false>), dim3(a.ntile), dim3(NW * 64), 0, s, a);
     FMM_HIP(hipGetLastError());
 }
 
 template <int FORM, int NRB = 1>
-int blocks_per_cu(int nrb) {
+int blocks_per_cu(int nrb, bool lean) {
     if constexpr (NRB <= 16) {
-        if (nrb != NRB) return blocks_per_cu<FORM, NRB + 1>(nrb);
+        if (nrb != NRB) return blocks_per_cu<FORM, NRB + 1>(nrb, lean);
         int n = 0;
         constexpr int NW = waves_for<NRB, FORM>();
-        FMM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_m2l<NRB, FORM, NW>, NW * 64, 0));
+        if constexpr (can_be_lean<NRB, FORM>())
+            if (lean) FMM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_m2l<NRB, FORM, NW, true>, NW * 64, 0));
+        if (n == 0) FMM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_m2l<NRB, FORM, NW, false>, NW * 64, 0));
         return n > 0 ? n : 1;
     } else {
         return 1;
@@ -598,13 +627,13 @@ void m2l_split_plain(int which, int r_pad, int64_t count, const float *in, uint1
     FMM_HIP(hipStreamSynchronize(s));
 }
 
-int m2l_blocks_per_cu(int form, int r_pad) {
+int m2l_blocks_per_cu(int form, int r_pad, bool lean) {
     FMM_REQUIRE(m2l_supported(r_pad), "m2l: unsupported state size");
     switch (form) {
-    case 0: return blocks_per_cu<0>(r_pad / 32);
-    case 3: return blocks_per_cu<3>(r_pad / 32);
-    case 4: return blocks_per_cu<4>(r_pad / 32);
-    case 6: return blocks_per_cu<6>(r_pad / 32);
+    case 0: return blocks_per_cu<0>(r_pad / 32, lean);
+    case 3: return blocks_per_cu<3>(r_pad / 32, lean);
+    case 4: return blocks_per_cu<4>(r_pad / 32, lean);
+    case 6: return blocks_per_cu<6>(r_pad / 32, lean);
     default: throw Error(FMM_ERR_ARG, "m2l: unknown arithmetic");
     }
 }

@@ -30,6 +30,7 @@ struct M2LLaunch {
     const int32_t *piece_slot = nullptr;  // per tile: -1, or the slot of partial it writes instead of adding to out
     float *partial = nullptr;             // [slot][ncol][r_pad]
     float *out = nullptr;
+    int lean = 0;        // float32 up to 192 rows: the kernel of fewer registers, three workgroups a CU
     int accumulate = 1;  // add to out; 0: write it (each vector belongs to one tile)
 };
 
@@ -37,7 +38,7 @@ int m2l_ncol(int r_pad);
 // M2L arithmetic ("form"): 0 float32; 6, 4 or 3 the split-BF16 part products
 // (bf16x6 of three parts; bf16x4 and bf16x3 of two parts)
 int m2l_form_parts(int form);                  // bfloat16 parts per value of a split form
-int m2l_blocks_per_cu(int form, int r_pad);    // workgroups of the kernel that fit on one CU
+int m2l_blocks_per_cu(int form, int r_pad, bool lean);  // workgroups of the kernel that fit on one CU
 // cut tiles: out[cols[t][c]] += sum over q < kpieces[t] of partial[slot0[t] + q][c] (q in order)
 void m2l_reduce(int r_pad, int ntile, int ncol, const int32_t *cols, const int32_t *slot0, const int32_t *kpieces,
                 const float *partial, float *out, bool accumulate, hipStream_t s);

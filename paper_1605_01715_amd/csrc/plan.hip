@@ -456,23 +456,24 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         // points, Chebyshev: 5677 us at 0.45, 5283 at 0.55, 5201 at 0.65),
         // except with matrices below 96 rows, where the partials are most of
         // a step (order 4, 400,000 points: 676 us at 0.45, 747 at 0.65), where
-        // the partials would pass 4 GiB, and where the dispatch would not end
-        // 5% sooner: in a 100,000-point cube, order 6, the 16 full tiles bound
-        // it whatever becomes of the other 24 (602 us, 703 at 0.65).
+        // the partials would pass 4 GiB, and where the translation would not
+        // end 3% sooner (as estimated below): in a 100,000-point cube, order
+        // 6, the 16 full tiles bound it whatever becomes of the other 24
+        // (602 us, 703 at 0.65).
         lap("m2l direction lists");
-        // The dispatch of tiles with nd directions on XCD oct, k pieces each:
+        // The dispatch of tiles with nd[x] directions on XCD x, k pieces each:
         // the longest XCD's makespan in steps, with a cost of 2 directions per
         // piece of a cut tile
-        const int slots = 32 * m2l_blocks_per_cu(P.m2l_form, P.r_pad);  // concurrent workgroups per XCD
-        auto makespan = [&](const std::vector<int> &nd, const std::vector<int> &oct, int k) {
+        using PerXcd = std::vector<std::vector<int>>;
+        int slots = 32 * m2l_blocks_per_cu(P.m2l_form, P.r_pad, true);  // concurrent workgroups per XCD
+        auto makespan = [&](const PerXcd &nd, int k) {
             double worst = 0.0;
 #pragma omp parallel for schedule(dynamic, 1) reduction(max : worst)
             for (int x = 0; x < 8; ++x) {
                 std::vector<double> w;
-                for (size_t tl = 0; tl < nd.size(); ++tl) {
-                    if (oct[tl] != x) continue;
-                    const int kk = std::min(k, nd[tl]);
-                    for (int q = 0; q < kk; ++q) w.push_back((double)nd[tl] / kk + (kk > 1 ? 2.0 : 0.0));
+                for (int n : nd[x]) {
+                    const int kk = std::min(k, n);
+                    for (int q = 0; q < kk; ++q) w.push_back((double)n / kk + (kk > 1 ? 2.0 : 0.0));
                 }
                 std::sort(w.begin(), w.end(), std::greater<double>());
                 std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
@@ -488,14 +489,40 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             }
             return worst;
         };
-        // the best of 1 to 6 pieces a tile, and its makespan
-        auto best_pieces = [&](const std::vector<int> &nd, const std::vector<int> &oct) {
-            std::pair<int, double> best{1, makespan(nd, oct, 1)};
+        // the best of 1 to 6 pieces a tile (or the forced number)
+        auto best_pieces = [&](const PerXcd &nd) {
+            if (P.opt.m2l_pieces) return P.opt.m2l_pieces;
+            int k_best = 1, longest = 0;
+            for (const auto &tiles : nd)
+                for (int n : tiles) longest = std::max(longest, n);
+            if (longest <= 1) return 1;  // nothing to cut
+            double best = makespan(nd, 1);
             for (int k = 2; k <= 6; ++k) {
-                const double m = makespan(nd, oct, k);
-                if (m < best.second * 0.995) best = {k, m};
+                const double m = makespan(nd, k);
+                if (m < best * 0.995) {
+                    best = m;
+                    k_best = k;
+                }
             }
-            return best;
+            return k_best;
+        };
+        // What bounds the translation, in steps of a CU's matrix cores: all
+        // the work over 256 CUs, and the longest piece. Where nothing else
+        // runs on its CU, a piece's step adds the wait for its copies, about
+        // the matrix work of three 32-row blocks in float32.
+        struct Bound {
+            double load, chain;
+        };
+        const double alone = 1.0 + 3.0 * 32 / P.r_pad;
+        auto bound = [&](const PerXcd &nd, int k) {
+            Bound b{0.0, 0.0};
+            for (const auto &tiles : nd)
+                for (int n : tiles) {
+                    const int kk = std::min(k, n);
+                    b.load += (n + (kk > 1 ? 2.0 * kk : 0.0)) / 256;
+                    if (n) b.chain = std::max(b.chain, alone * ((double)n / kk + (kk > 1 ? 2.0 : 0.0)));
+                }
+            return b;
         };
         double pair_fill = 0.45;
         std::vector<int64_t> tlive(ntile, 0);
@@ -505,30 +532,29 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             const int64_t n = toff[tl + 1] - toff[tl];
             return n > 0 && (double)tlive[tl] < fill * (double)n * nc;
         };
-        if (P.m2l_form == 0 && P.r_pad >= 96) {
-            // the makespan with the tiles below `fill` as pair tiles, and the pair tiles' count
+        bool between = false;  // is there a tile that the two lines treat differently?
+        for (int tl = 0; tl < ntile; ++tl) between |= sparse_at(tl, 0.65) && !sparse_at(tl, pair_fill);
+        if (P.m2l_form == 0 && P.r_pad >= 96 && between) {
+            // the larger bound with the tiles below `fill` as pair tiles, and the pair tiles' count
             auto span_at = [&](double fill, int64_t &npair) {
-                std::vector<int> nd, oct;
+                PerXcd nd(8);
                 std::vector<int64_t> pairs(kNumDirs, 0);
                 for (int tl = 0; tl < ntile; ++tl) {
                     if (sparse_at(tl, fill)) {
                         for (int d = 0; d < kNumDirs; ++d) pairs[d] += tcnt[(size_t)tl * kNumDirs + d];
                     } else {
-                        nd.push_back((int)(toff[tl + 1] - toff[tl]));
-                        oct.push_back(tile_oct[tl]);
+                        nd[tile_oct[tl]].push_back((int)(toff[tl + 1] - toff[tl]));
                     }
                 }
                 npair = 0;
                 for (int d = 0; d < kNumDirs; ++d) npair += (pairs[d] + nc - 1) / nc;
-                for (int64_t i = 0; i < npair; ++i) {
-                    nd.push_back(1);
-                    oct.push_back((int)(i % 8));
-                }
-                return best_pieces(nd, oct).second;
+                for (int64_t i = 0; i < npair; ++i) nd[i % 8].push_back(1);
+                const Bound b = bound(nd, best_pieces(nd));
+                return std::max(b.load, b.chain);
             };
             int64_t n45, n65;
             const double s45 = span_at(0.45, n45), s65 = span_at(0.65, n65);
-            if (s65 < 0.95 * s45 && n65 * nc * P.r_pad * (int64_t)sizeof(float) <= (int64_t)4 << 30) pair_fill = 0.65;
+            if (s65 < 0.97 * s45 && n65 * nc * P.r_pad * (int64_t)sizeof(float) <= (int64_t)4 << 30) pair_fill = 0.65;
         }
         std::vector<uint8_t> pair_tile(ntile, 0);
         {
@@ -637,12 +663,36 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         // sums, added to the output in piece order by a second kernel.
         {
             auto ndir = [&](int tl) { return (int)(toff[tl + 1] - toff[tl]); };
-            int kbest = P.opt.m2l_pieces;  // forced, or 0: simulated
-            if (kbest == 0) {
-                std::vector<int> nd(ntile);
-                for (int tl = 0; tl < ntile; ++tl) nd[tl] = ndir(tl);
-                kbest = best_pieces(nd, tile_oct).first;
+            PerXcd nd(8);
+            for (int tl = 0; tl < ntile; ++tl) nd[tile_oct[tl]].push_back(ndir(tl));
+            int kbest = best_pieces(nd);
+            Bound b = bound(nd, kbest);
+            // The lean kernel, where there is one: three workgroups a CU cover
+            // each other's start, copies and stores better than two (4096
+            // points, order 6: 140 -> 134 us; 400,000, order 4: 808 -> 731).
+            // Not where the longest piece bounds the translation: it has a
+            // larger share of its CU among two (200,000-point cloud, order 6:
+            // 1113 us, 1210 lean).
+            P.m2l_lean = b.load >= b.chain;
+            const int fewer = P.m2l_lean || P.m2l_form ? slots : 32 * m2l_blocks_per_cu(P.m2l_form, P.r_pad, false);
+            if (fewer != slots) {
+                slots = fewer;
+                kbest = best_pieces(nd);
+                b = bound(nd, kbest);
             }
+            // Float32 and bf16x6 translations that keep every CU busy for three
+            // steps or more, and longer than their longest piece, are bound by
+            // the matrix cores: a leaf evaluation beside them delays them by
+            // what it takes, but one launched after them fills the gaps of the
+            // reduction, the gather and the downward pass. After instead of beside:
+            // 300,000-point cloud, order 8, bf16x6 1600 -> 1448 us; eight
+            // spheres 690 -> 684; uniform 400,000, order 6 3275 -> 3071. Where
+            // CUs run out of tiles the evaluation is welcome beside them (4096
+            // points 134 us, after 138; cloud of 200,000, order 6 1116,
+            // 1198), as it is beside the shorter bf16x3 steps that wait on
+            // memory (field of 300 spheres 617, 822) and those of matrices
+            // below 96 rows (order 4, 100,000 points 313, 383).
+            P.eval_after_m2l = (P.m2l_form == 0 || P.m2l_form == 6) && P.r_pad >= 96 && b.load >= 3.0 && b.load >= b.chain;
             lap("m2l pair tiles and piece model");
             P.m2l_pieces_per_tile = kbest;
             // pieces: (tile, first direction, last direction + 1, partial slot or -1)
@@ -1204,36 +1254,6 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
     g.centre = t.centre.p;
     g.half = t.half.p;
 
-    auto split_m2l_input = [&] {
-        if (P.m2l_form) m2l_split_vecs(P.ut.p, rp, t.nb * nrhs, m2l_form_parts(P.m2l_form), P.ut_bf.p, s);
-    };
-    auto run_m2l = [&] {
-        M2LLaunch m;
-        m.r_pad = rp;
-        m.ntile = P.m2l_ntile;
-        m.ncol = P.m2l_ncol;
-        m.tile_term_off = P.m2l_toff.p;
-        m.term_dir = P.m2l_dir.p;
-        m.term_src = P.m2l_src.p;
-        m.tile_cols = P.m2l_cols.p;
-        m.mats = op.m2l_f32.p;
-        m.in = P.ut.p;
-        m.mats_bf = m2l_form_parts(P.m2l_form) == 3 ? op.m2l_bf.p : op.m2l_bf2.p;
-        m.in_bf = P.ut_bf.p;
-        m.zero = P.m2l_zero.p;
-        m.piece_slot = P.m2l_slot.p;
-        m.partial = P.m2l_partial.p;
-        m.out = P.dt.p;
-        m.accumulate = P.cheb ? 0 : 1;
-        m2l_run(P.m2l_form, m, s);
-        if (P.m2l_nsplit > 0)
-            m2l_reduce(rp, P.m2l_nsplit, P.m2l_ncol, P.m2l_red_cols.p, P.m2l_red_slot0.p, P.m2l_red_k.p, P.m2l_partial.p,
-                       P.dt.p, !P.cheb, s);
-        if (P.m2l_ngather > 0)
-            m2l_gather(rp, P.m2l_ngather, P.m2l_gt.p, P.m2l_goff.p, P.m2l_gidx.p, P.m2l_partial.p, P.dt.p, !P.cheb,
-                       s);
-    };
-
     EvalArgs e;
     e.wleaf = P.wleaf.p;
     e.wt0 = P.wt0.p;
@@ -1268,6 +1288,50 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
     e.delta2 = std::max(P.opt.cutoff * P.opt.cutoff, std::numeric_limits<float>::min());
     e.pot = pot;
     e.field = field;
+    // the leaf evaluation on the side stream, from this point of the caller's
+    auto fork_eval = [&] {
+        FMM_HIP(hipEventRecord(P.fork, s));
+        FMM_HIP(hipStreamWaitEvent(P.side, P.fork, 0));
+        if (ts) FMM_HIP(hipEventRecord(ts->side[2], P.side));
+        EvalArgs en = e;
+        if (!P.cheb) en.surf_mask = 2;  // M2P surfaces and the point ranges; L2P is a pass of its own
+        eval_leaves(nrhs, sl, dl, en, g, src, P.side);
+        if (ts) FMM_HIP(hipEventRecord(ts->side[3], P.side));
+        FMM_HIP(hipEventRecord(P.join, P.side));
+    };
+
+    auto split_m2l_input = [&] {
+        if (P.m2l_form) m2l_split_vecs(P.ut.p, rp, t.nb * nrhs, m2l_form_parts(P.m2l_form), P.ut_bf.p, s);
+    };
+    auto run_m2l = [&] {
+        M2LLaunch m;
+        m.r_pad = rp;
+        m.ntile = P.m2l_ntile;
+        m.ncol = P.m2l_ncol;
+        m.tile_term_off = P.m2l_toff.p;
+        m.term_dir = P.m2l_dir.p;
+        m.term_src = P.m2l_src.p;
+        m.tile_cols = P.m2l_cols.p;
+        m.mats = op.m2l_f32.p;
+        m.in = P.ut.p;
+        m.mats_bf = m2l_form_parts(P.m2l_form) == 3 ? op.m2l_bf.p : op.m2l_bf2.p;
+        m.in_bf = P.ut_bf.p;
+        m.zero = P.m2l_zero.p;
+        m.piece_slot = P.m2l_slot.p;
+        m.partial = P.m2l_partial.p;
+        m.out = P.dt.p;
+        m.accumulate = P.cheb ? 0 : 1;
+        m.lean = P.m2l_lean ? 1 : 0;
+        m2l_run(P.m2l_form, m, s);
+        if (P.eval_after_m2l) fork_eval();
+        if (P.m2l_nsplit > 0)
+            m2l_reduce(rp, P.m2l_nsplit, P.m2l_ncol, P.m2l_red_cols.p, P.m2l_red_slot0.p, P.m2l_red_k.p, P.m2l_partial.p,
+                       P.dt.p, !P.cheb, s);
+        if (P.m2l_ngather > 0)
+            m2l_gather(rp, P.m2l_ngather, P.m2l_gt.p, P.m2l_goff.p, P.m2l_gidx.p, P.m2l_partial.p, P.dt.p, !P.cheb,
+                       s);
+    };
+
     // P2L needs only the points: it runs first on the side stream, beside P2M
     // and M2M (without X-list work the streams are not tied together here)
     const bool p2l = P.n_p2l > 0 || ts;
@@ -1287,7 +1351,8 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
         // Chebyshev form (Sec. III.A.1 Eq. p2m): node weights W (phi_u) up the
         // tree, node values L (phi_d) down; M2L in the shared compressed basis.
         // The leaf evaluation needs W only (M2P), so it runs on the side stream
-        // from the end of the upward pass, beside P2L, M2L and L2L, and writes
+        // from the end of the upward pass, or of the M2L kernel
+        // (eval_after_m2l), beside what follows there, and writes
         // the outputs; L2P adds to them after the join. The node values need
         // no clearing: P2L writes its boxes', the expansion overwrites every
         // other box the downward pass reads (all boxes with targets from
@@ -1308,12 +1373,7 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
         dense_gemm_f32(rp, np, P.cheb_compress.ntile, P.cheb_compress.cols.p, op.pv_f32.p, P.phi_u.p, P.ut.p,
                        nullptr, 0, s, nullptr, P.m2l_form ? P.ut_bf.p : nullptr, m2l_form_parts(P.m2l_form));
         // side stream, second: the leaf evaluation, beside M2L and L2L
-        FMM_HIP(hipEventRecord(P.fork, s));
-        FMM_HIP(hipStreamWaitEvent(P.side, P.fork, 0));
-        if (ts) FMM_HIP(hipEventRecord(ts->side[2], P.side));
-        eval_leaves(nrhs, sl, dl, e, g, src, P.side);
-        if (ts) FMM_HIP(hipEventRecord(ts->side[3], P.side));
-        FMM_HIP(hipEventRecord(P.join, P.side));
+        if (!P.eval_after_m2l) fork_eval();
         mark(ST_P2L);  // (P2L runs on the side stream; timed there)
         mark(ST_M2L);
         run_m2l();
@@ -1335,7 +1395,8 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
     } else {
         // Surface form: the near field and M2P (the leaf evaluation without
         // L2P) need only the upward equivalent densities, so after the upward
-        // pass they run on the side stream beside M2L, L2L and the downward
+        // pass (eval_after_m2l: the M2L kernel) they run on the side stream
+        // beside M2L, L2L and the downward
         // expansion; L2P adds to the outputs after the join. P2L and its
         // projection onto the M2L output run there first: queued on the
         // caller's stream after the fork they waited for wave slots behind the
@@ -1354,14 +1415,7 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
         mark(ST_M2M);
         for (auto &j : P.m2m_jobs) run_gemm(j, op.m2m_f64.p, rp, rp, P.ut.p, P.ut.p, nullptr, false, s);
         run_gemm(P.c2e_up, op.cu_f64.p, np, rp, P.ut.p, P.phi_u.p, P.col_scale.p, false, s);
-        FMM_HIP(hipEventRecord(P.fork, s));
-        FMM_HIP(hipStreamWaitEvent(P.side, P.fork, 0));
-        if (ts) FMM_HIP(hipEventRecord(ts->side[2], P.side));
-        EvalArgs en = e;
-        en.surf_mask = 2;  // M2P surfaces and the point ranges
-        eval_leaves(nrhs, sl, dl, en, g, src, P.side);
-        if (ts) FMM_HIP(hipEventRecord(ts->side[3], P.side));
-        FMM_HIP(hipEventRecord(P.join, P.side));
+        if (!P.eval_after_m2l) fork_eval();
         mark(ST_P2L);  // (P2L runs on the side stream; timed there)
         wait_p2l();
         mark(ST_M2L);
