@@ -347,6 +347,126 @@ __global__ __launch_bounds__(64) void k_nodes_to_points(const double *coef, Eval
     }
 }
 
+// L2P with 8 nodes a side: one wave per item, 16 targets at a time. The z sum
+// of every (i, j) is a matrix product, 64 (i, j) x 8 nodes by 8 x 16 targets, in
+// v_mfma_f64_16x16x4_f64: the node values are held in registers, converted
+// once per item, where one lane per target read all 512 from LDS and converted
+// them in every lane. The rows are dealt so that lane group g = 2 ga + gb
+// (lane = 16 g + target) gets the sums of half ga of the x nodes and half gb of
+// the y nodes and needs 4 + 4 + 2 of the 24 one-dimensional weights, five
+// mirrored pairs; the groups' shares of a target are added across lanes at the
+// end. Bound by latency and the reads of the coefficients from LDS. Measured,
+// one lane per target -> this: 99,230 items (4M points) 308 -> 210 us; 35,709
+// items, three right-hand sides 178 -> 105; 8535 items with the field 64 -> 38.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+template <int NRHS, bool FIELD>
+__global__ __launch_bounds__(64, NRHS > 2 ? 3 : 4) void k_nodes_to_points8(const double *coef, EvalArgs a, SurfaceGeom g, const float *L) {
+    constexpr int N = 8;
+    __shared__ __align__(16) double cf[N * N];
+    const int lane = threadIdx.x, c16 = lane & 15, grp = lane >> 4, ga = grp >> 1, gb = grp & 1;
+    const int leaf = a.wleaf[blockIdx.x];
+    const int64_t t_first = a.tbeg[leaf] + a.wt0[blockIdx.x];
+    const int nt = (int)min((int64_t)64, a.tend[leaf] - t_first);
+    cf[lane] = coef[lane];
+    // node v of the half h of an axis: the pairs n, 7 - n of n = 2 h, 2 h + 1
+    auto node = [](int h, int v) { return v & 1 ? 7 - (2 * h + (v >> 1)) : 2 * h + (v >> 1); };
+    // A fragments: row c16 of block ii is i = node(row >> 1 & 1, ii), j = node(row & 1, row >> 2);
+    // the product of step s takes k = grp, then 7 - grp
+    double av[NRHS][4][2];
+#pragma unroll
+    for (int r = 0; r < NRHS; ++r)
+#pragma unroll
+        for (int ii = 0; ii < 4; ++ii) {
+            const int i = node(c16 >> 1 & 1, ii), j = node(c16 & 1, c16 >> 2);
+            const float *v = L + ((int64_t)leaf * NRHS + r) * g.n_pad + (i * N + j) * N;
+            av[r][ii][0] = (double)v[grp];
+            av[r][ii][1] = (double)v[7 - grp];
+        }
+    const double ih = 1.0 / g.half[leaf];
+    const double cx = g.centre[3 * leaf], cy = g.centre[3 * leaf + 1], cz = g.centre[3 * leaf + 2];
+    __syncthreads();
+#pragma unroll 1
+    for (int t0 = 0; t0 < nt; t0 += 16) {
+        asm volatile("" ::: "memory");  // the coefficients stay in LDS: 80 of them would take 160 registers
+        const bool valid = t0 + c16 < nt;
+        const int64_t k = t_first + (valid ? t0 + c16 : 0);
+        const int64_t dst = a.trg_perm ? a.trg_perm[k] : k;
+        double tk[N], dtk[N];
+        // S and dS of nodes n and 7 - n, mirror images, for the basis values
+        // in tk: the sums over even and odd degrees, added and subtracted
+        auto lagrange = [&](int n, double *v, double *dv) {
+            double e[2] = {0.0, 0.0}, de[2] = {0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                const double c = cf[n * N + q];
+                e[q & 1] += c * tk[q];
+                if (FIELD) de[q & 1] += c * dtk[q];
+            }
+            v[0] = e[0] + e[1];
+            v[1] = e[0] - e[1];
+            if (FIELD) {
+                dv[0] = de[0] + de[1];
+                dv[1] = de[0] - de[1];
+            }
+        };
+        double sx[4], sy[4], sz[2], dsx[4], dsy[4], dsz[2];
+        cheb_basis<N, FIELD>(((double)a.tz[k] - cz) * ih, tk, dtk);
+        lagrange(grp, sz, dsz);
+        cheb_basis<N, FIELD>(((double)a.ty[k] - cy) * ih, tk, dtk);
+        lagrange(2 * gb, sy, dsy);
+        lagrange(2 * gb + 1, sy + 2, dsy + 2);
+        cheb_basis<N, FIELD>(((double)a.tx[k] - cx) * ih, tk, dtk);
+        lagrange(2 * ga, sx, dsx);
+        lagrange(2 * ga + 1, sx + 2, dsx + 2);
+#pragma unroll
+        for (int r = 0; r < NRHS; ++r) {
+            double o[4] = {0.0, 0.0, 0.0, 0.0};  // potential, then its gradient in t
+#pragma unroll
+            for (int ii = 0; ii < 4; ++ii) {
+                f64x4 c = {0.0, 0.0, 0.0, 0.0}, cd = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    c = __builtin_amdgcn_mfma_f64_16x16x4f64(av[r][ii][s], sz[s], c, 0, 0, 0);
+                    if (FIELD) cd = __builtin_amdgcn_mfma_f64_16x16x4f64(av[r][ii][s], dsz[s], cd, 0, 0, 0);
+                }
+                double b = 0.0, by = 0.0, bz = 0.0;
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) {
+                    b += sy[jj] * c[jj];
+                    if (FIELD) {
+                        by += dsy[jj] * c[jj];
+                        bz += sy[jj] * cd[jj];
+                    }
+                }
+                o[0] += sx[ii] * b;
+                if (FIELD) {
+                    o[1] += dsx[ii] * b;
+                    o[2] += sx[ii] * by;
+                    o[3] += sx[ii] * bz;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < (FIELD ? 4 : 1); ++q) {
+                o[q] += __shfl_xor(o[q], 16);
+                o[q] += __shfl_xor(o[q], 32);
+            }
+            if (!valid) continue;
+            if (grp == 0) {
+                if (a.pot) {
+                    float *pp = a.pot + r * a.n_trg + dst;
+                    *pp = a.accumulate ? (float)((double)*pp + o[0]) : (float)o[0];
+                }
+            } else if (FIELD && a.field) {
+                // field = -grad_x f = -(1/h) grad_t f, one component from each group
+                float *f = a.field + ((int64_t)r * a.n_trg + dst) * 3 + (grp - 1);
+                const double gr = -ih * (grp == 1 ? o[1] : grp == 2 ? o[2] : o[3]);
+                *f = a.accumulate ? (float)((double)*f + gr) : (float)gr;
+            }
+        }
+    }
+}
+
 // out (+)= (A_x (x) A_y (x) A_z) in with A_c = S[side_c] (M2M) or its
 // transpose (L2L). Lane (q, s) = (lane / N, lane % N): the z pass gives
 // T1[p'][q][s] (to LDS), the y pass T2[p'] for the lane's (q, s) in
@@ -533,15 +653,25 @@ void cheb_tensor(int nrhs, int n, bool l2l, const double *s1, int nitems, const 
     FMM_HIP(hipGetLastError());
 }
 
+// 8 nodes a side fill the matrix tiles (64 x 8); other orders pad rows or k
+template <int N, int R, bool FIELD>
+static void launch_nodes_to_points(dim3 gr, dim3 bl, hipStream_t s, const double *coef, const EvalArgs &a,
+                                   const SurfaceGeom &g, const float *L) {
+    if constexpr (N == 8)
+        hipLaunchKernelGGL((k_nodes_to_points8<R, FIELD>), gr, bl, 0, s, coef, a, g, L);
+    else
+        hipLaunchKernelGGL((k_nodes_to_points<N, R, FIELD>), gr, bl, 0, s, coef, a, g, L);
+}
+
 void nodes_to_points(int nrhs, int n, const double *coef, const EvalArgs &a, const SurfaceGeom &g, const float *L,
                      hipStream_t s) {
     if (a.nwork <= 0) return;
     FMM_REQUIRE(g.ns == n * n * n && g.n_pad >= g.ns, "nodes_to_points: node count does not match the order");
     dim3 gr(a.nwork), bl(64);
     if (a.field) {
-        FMM_CHEB_SWITCH(n, nrhs, hipLaunchKernelGGL((k_nodes_to_points<N, R, true>), gr, bl, 0, s, coef, a, g, L));
+        FMM_CHEB_SWITCH(n, nrhs, (launch_nodes_to_points<N, R, true>(gr, bl, s, coef, a, g, L)));
     } else {
-        FMM_CHEB_SWITCH(n, nrhs, hipLaunchKernelGGL((k_nodes_to_points<N, R, false>), gr, bl, 0, s, coef, a, g, L));
+        FMM_CHEB_SWITCH(n, nrhs, (launch_nodes_to_points<N, R, false>(gr, bl, s, coef, a, g, L)));
     }
     FMM_HIP(hipGetLastError());
 }
