@@ -341,7 +341,7 @@ typedef struct {
                                             and rhs */
     int64_t m2l_pieces;                  /* M2L work items per tile of 128 target boxes (load
                                             balance across CUs; pieces add up in a fixed order) */
-    int64_t m2l_pair_tiles;              /* M2L work items of one direction whose columns are
+    int64_t m2l_pair_tiles;              /* M2L work items of one to four directions whose columns are
                                             (target, source) pairs (sparse V lists) */
     int64_t basis;                       /* FMM_BASIS_* of the plan */
     double root[4];                      /* root cube actually used */

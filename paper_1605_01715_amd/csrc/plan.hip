@@ -441,8 +441,8 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         // partners (points on surfaces), a tile runs every direction for
         // only a fraction of its columns (fill 0.2-0.3 on the sphere
         // workloads). The (direction, target) pairs of tiles with fill below
-        // pair_fill are regrouped by direction into tiles of one direction
-        // whose columns are pairs, all live; each writes its
+        // pair_fill are regrouped into tiles of one direction, or of a few
+        // neighbouring ones, whose columns are live for all of them; each writes its
         // products to a partial-sum slot, and a gather adds each target's
         // partials in direction order. Costs: a tile does 6 steps per
         // direction; a pair tile 6 steps plus writing and reading back its
@@ -461,9 +461,10 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         // 6, the 16 full tiles bound it whatever becomes of the other 24
         // (602 us, 703 at 0.65).
         lap("m2l direction lists");
-        // The dispatch of tiles with nd[x] directions on XCD x, k pieces each:
-        // the longest XCD's makespan in steps, with a cost of 2 directions per
-        // piece of a cut tile
+        // The dispatch of tiles with nd[x] directions on XCD x, k pieces each
+        // (pair tiles, in one piece: the negative count): the longest XCD's
+        // makespan in steps, with a cost of 2 directions per piece of a cut
+        // tile
         using PerXcd = std::vector<std::vector<int>>;
         int slots = 32 * m2l_blocks_per_cu(P.m2l_form, P.r_pad, true);  // concurrent workgroups per XCD
         auto makespan = [&](const PerXcd &nd, int k) {
@@ -472,7 +473,8 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             for (int x = 0; x < 8; ++x) {
                 std::vector<double> w;
                 for (int n : nd[x]) {
-                    const int kk = std::min(k, n);
+                    const int kk = n < 0 ? 1 : std::min(k, n);
+                    n = std::abs(n);
                     for (int q = 0; q < kk; ++q) w.push_back((double)n / kk + (kk > 1 ? 2.0 : 0.0));
                 }
                 std::sort(w.begin(), w.end(), std::greater<double>());
@@ -518,7 +520,8 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             Bound b{0.0, 0.0};
             for (const auto &tiles : nd)
                 for (int n : tiles) {
-                    const int kk = std::min(k, n);
+                    const int kk = n < 0 ? 1 : std::min(k, n);
+                    n = std::abs(n);
                     b.load += (n + (kk > 1 ? 2.0 * kk : 0.0)) / 256;
                     if (n) b.chain = std::max(b.chain, alone * ((double)n / kk + (kk > 1 ? 2.0 : 0.0)));
                 }
@@ -584,60 +587,125 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
                     oct2.push_back(tile_oct[tl]);
                     pair2.push_back(0);
                 }
-                // the (direction, target) pairs ordered by direction, then target:
-                // a counting sort over the directions of the targets taken in
-                // increasing order, in parallel over chunks of the targets
+                // A target's live directions among G neighbouring ones (G = 1, 2
+                // or 4; directions are numbered along z, so neighbours are
+                // often live together) are one column of one tile: the targets
+                // are grouped by (group of directions, live subset), a tile
+                // runs the subset's directions, and each target's products
+                // leave it as one partial sum instead of up to G. More, finer
+                // groups leave more tiles half empty, so G is the one that
+                // makes the cost least, a tile's directions plus the start and
+                // the partial sums, which weigh about one more float32 or
+                // bf16x6 direction and two to three of the shorter ones; 1
+                // where one tile per workgroup slot is enough, as the longest
+                // tile then sets the time (4096 points: 133 us, 140 with G =
+                // 2). Measured against one direction a tile: 48 bodies, three
+                // right-hand sides, bf16x3, G = 4 3.99 -> 3.43 ms (2: 3.68);
+                // 300,000-point cloud, order 6, float32, G = 2 1448 -> 1340
+                // us; field of 300 spheres, G = 2 572 -> 552 (4: 557); 4M
+                // points, G = 4 7.64 -> 7.54 ms; eight spheres, G = 2 686 ->
+                // 677 (4: 762).
                 std::sort(sparse.begin(), sparse.end());
                 const int nchunk = (int)std::max<size_t>(1, std::min<size_t>(64, sparse.size() / 64));
                 auto chunk_at = [&](int k) { return sparse.size() * (size_t)k / (size_t)nchunk; };
-                std::vector<int64_t> pos((size_t)nchunk * kNumDirs, 0), start(kNumDirs + 1, 0);
-                auto each_dir = [&](int32_t v, auto &&f) {
+                static_assert(kNumDirs % 4 == 0, "groups of four directions");
+                constexpr int kMaxClass = kNumDirs / 4 * 16;  // the most (group, subset) classes of any G
+                // f(class) of every group of g directions where target v has sources; class = group 2^g + subset,
+                // the subset's first direction in its highest bit
+                auto each_class = [&](int32_t v, int g, auto &&f) {
                     const uint64_t *m = mask_of(v / nrhs);
-                    for (int w = 0; w < kMaskWords; ++w)
-                        for (uint64_t bits = m[w]; bits; bits &= bits - 1) f(w * 64 + 63 - __builtin_ctzll(bits));
+                    for (int w = 0; w < kMaskWords; ++w) {
+                        if (!m[w]) continue;
+                        for (int at = 0; at < 64; at += g) {
+                            const int sub = (int)(m[w] >> (64 - g - at)) & ((1 << g) - 1);
+                            if (sub) f(((w * 64 + at) / g << g) + sub);
+                        }
+                    }
                 };
+                std::vector<int64_t> pos((size_t)nchunk * kMaxClass), start(kMaxClass + 1);
+                auto count = [&](int g) {
+                    std::fill(pos.begin(), pos.end(), 0);
 #pragma omp parallel for schedule(dynamic, 1)
-                for (int k = 0; k < nchunk; ++k)
-                    for (size_t i = chunk_at(k); i < chunk_at(k + 1); ++i)
-                        each_dir(sparse[i], [&](int d) { ++pos[(size_t)k * kNumDirs + d]; });
-                for (int d = 0; d < kNumDirs; ++d) {
-                    int64_t run = start[d];
+                    for (int k = 0; k < nchunk; ++k)
+                        for (size_t i = chunk_at(k); i < chunk_at(k + 1); ++i)
+                            each_class(sparse[i], g, [&](int c) { ++pos[(size_t)k * kMaxClass + c]; });
+                };
+                count(4);
+                int G = 1;
+                {
+                    const double extra = P.m2l_form == 0 || P.m2l_form == 6 ? 1.2 : 2.5;
+                    std::vector<int64_t> n4(kMaxClass, 0);
+                    for (int k = 0; k < nchunk; ++k)
+                        for (int c = 0; c < kMaxClass; ++c) n4[c] += pos[(size_t)k * kMaxClass + c];
+                    double best = 0.0;
+                    int64_t tiles1 = 0;  // one direction each
+                    for (int g = 1; g <= (g == 1 || tiles1 > 8 * slots ? 4 : 1); g *= 2) {
+                        std::vector<int64_t> n(kNumDirs / g << g, 0);
+                        for (int c = 0; c < kMaxClass; ++c)
+                            for (int at = 0; n4[c] && at < 4; at += g) {
+                                const int sub = (c & 15) >> (4 - g - at) & ((1 << g) - 1);
+                                if (sub) n[(((c >> 4) * 4 + at) / g << g) + sub] += n4[c];
+                            }
+                        double cost = 0.0;
+                        for (size_t c = 0; c < n.size(); ++c)
+                            cost += (double)((n[c] + nc - 1) / nc) *
+                                    (__builtin_popcount((unsigned)c & ((1u << g) - 1)) + extra);
+                        if (g == 1)
+                            for (int64_t n1 : n) tiles1 += (n1 + nc - 1) / nc;
+                        if (g == 1 || cost < best) {
+                            best = cost;
+                            G = g;
+                        }
+                    }
+                }
+                if (G != 4) count(G);
+                // a counting sort over the classes of the targets taken in
+                // increasing order, in parallel over chunks of the targets
+                const int nclass = kNumDirs / G << G;
+                for (int c = 0; c < nclass; ++c) {
+                    int64_t run = start[c];
                     for (int k = 0; k < nchunk; ++k) {
-                        const int64_t n = pos[(size_t)k * kNumDirs + d];
-                        pos[(size_t)k * kNumDirs + d] = run;
+                        const int64_t n = pos[(size_t)k * kMaxClass + c];
+                        pos[(size_t)k * kMaxClass + c] = run;
                         run += n;
                     }
-                    start[d + 1] = run;
+                    start[c + 1] = run;
                 }
-                std::vector<int32_t> by_dir(start[kNumDirs]);
+                std::vector<int32_t> by_class(start[nclass]);
 #pragma omp parallel for schedule(dynamic, 1)
                 for (int k = 0; k < nchunk; ++k)
                     for (size_t i = chunk_at(k); i < chunk_at(k + 1); ++i)
-                        each_dir(sparse[i], [&](int d) { by_dir[pos[(size_t)k * kNumDirs + d]++] = sparse[i]; });
-                // Tiles of nc pairs of one direction, in direction order. The
+                        each_class(sparse[i], G,
+                                   [&](int c) { by_class[pos[(size_t)k * kMaxClass + c]++] = sparse[i]; });
+                // Tiles of nc targets of one class, in direction order. The
                 // matrix depends on the direction only, so a tile takes the
-                // pairs of all octants (per octant, small plans had 1512 tiles
+                // targets of all octants (per octant, small plans had 1512 tiles
                 // of a few columns each: 14% of them used on 39,200 points on
                 // 40 spheres, 6% on a body of 14,700). XCD x gets a contiguous
                 // run of the tiles that brings its direction count, with that
                 // of its octant's own tiles, up to an even share.
+                auto subset = [&](int c) { return (unsigned)c & ((1u << G) - 1); };
                 int64_t npair = 0, xload[8] = {0, 0, 0, 0, 0, 0, 0, 0}, all = 0;
-                for (int d = 0; d < kNumDirs; ++d) npair += (start[d + 1] - start[d] + nc - 1) / nc;
+                for (int c = 0; c < nclass; ++c) {
+                    const int64_t n = (start[c + 1] - start[c] + nc - 1) / nc;
+                    npair += n;
+                    all += n * __builtin_popcount(subset(c));
+                }
                 for (size_t tl = 0; tl < oct2.size(); ++tl) xload[oct2[tl]] += toff2[tl + 1] - toff2[tl];
                 for (int x = 0; x < 8; ++x) all += xload[x];
-                all += npair;
                 cols2.reserve(cols2.size() + (size_t)npair * nc);
                 int x = 0;
-                for (int d = 0; d < kNumDirs; ++d)
-                    for (int64_t i = start[d]; i < start[d + 1]; i += nc) {
+                for (int c = 0; c < nclass; ++c)
+                    for (int64_t i = start[c]; i < start[c + 1]; i += nc) {
                         while (x < 7 && xload[x] * 8 >= all) ++x;
-                        ++xload[x];
-                        const int64_t j = std::min(start[d + 1], i + nc);
-                        tdir2.push_back(d);
+                        xload[x] += __builtin_popcount(subset(c));
+                        const int64_t j = std::min(start[c + 1], i + nc);
+                        for (int at = 0; at < G; ++at)
+                            if (subset(c) >> (G - 1 - at) & 1) tdir2.push_back((c >> G) * G + at);
                         toff2.push_back((int64_t)tdir2.size());
                         oct2.push_back(x);
                         pair2.push_back(1);
-                        cols2.insert(cols2.end(), by_dir.begin() + i, by_dir.begin() + j);
+                        cols2.insert(cols2.end(), by_class.begin() + i, by_class.begin() + j);
                         cols2.resize(cols2.size() + (size_t)(i + nc - j), -1);
                     }
                 toff.swap(toff2);
@@ -664,7 +732,7 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         {
             auto ndir = [&](int tl) { return (int)(toff[tl + 1] - toff[tl]); };
             PerXcd nd(8);
-            for (int tl = 0; tl < ntile; ++tl) nd[tile_oct[tl]].push_back(ndir(tl));
+            for (int tl = 0; tl < ntile; ++tl) nd[tile_oct[tl]].push_back(pair_tile[tl] ? -ndir(tl) : ndir(tl));
             int kbest = best_pieces(nd);
             Bound b = bound(nd, kbest);
             // The lean kernel, where there is one: three workgroups a CU cover
@@ -709,7 +777,7 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             for (int tl = 0; tl < ntile; ++tl) {
                 const int n = ndir(tl), kk = std::max(1, std::min(kbest, n));
                 if (n == 0) continue;
-                if (pair_tile[tl]) {  // one direction, its own slot, summed by the gather
+                if (pair_tile[tl]) {  // one piece, its own slot, summed by the gather
                     const int slot = nslot++;
                     for (int c = 0; c < nc; ++c) {
                         const int32_t v = cols[(size_t)tl * nc + c];

@@ -37,3 +37,21 @@ def test_tile_choices(shape, order, basis, bound, precision):
         f"{r['info']['rank']}, {k} pieces, rel L2 {l2:.2e}, worst {worst:.2e}")
     assert 1 <= k <= 6
     assert l2 < bound and worst < 100 * bound
+
+
+@pytest.mark.parametrize("n", [3000, 20_000, 60_000])
+@pytest.mark.parametrize("order,basis,nrhs,precision,bound", [(6, 0, 1, 0, 5e-5), (6, 0, 3, 1, 5e-5), (6, 1, 3, 2, 5e-4)])
+def test_grouped_directions(n, order, basis, nrhs, precision, bound):
+    """Points on a sphere: sparse lists throughout, few enough tiles for one
+    direction each at 3000 points, neighbouring directions sharing tiles beyond."""
+    rng = np.random.default_rng(n)
+    x = rng.standard_normal((n, 3))
+    x = (0.5 + 0.45 * x / np.linalg.norm(x, axis=1, keepdims=True)).astype(np.float32)
+    q = rng.standard_normal((nrhs, n)).astype(np.float32)
+    r = fmm_run(x, q=q, order=order, leaf=16, root=(0.0, 0.0, 0.0, 1.0), nrhs=nrhs, basis=basis, precision=precision)
+    say(f"test_grouped_directions: n={n} basis={basis} nrhs={nrhs} precision={precision}: {r['info']['n_boxes']} boxes")
+    for k in range(nrhs):
+        ref, _ = D.direct_sum(x[:2000], x, q[k])
+        l2, worst = errors(r["pot"][k][:2000], ref)
+        say(f"  rel L2 {l2:.2e}, worst {worst:.2e}")
+        assert l2 < bound and worst < 100 * bound
