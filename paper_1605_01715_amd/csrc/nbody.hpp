@@ -28,22 +28,21 @@ void points_to_surface(int nrhs, bool sl, bool dl, const int32_t *items, int nit
                        const int32_t *rng, double rfac, const SurfaceGeom &g, const PointSrc &src, float *out,
                        bool accumulate, hipStream_t s);
 
-// Leaf evaluation (L2P + M2P + P2P). Work item i is leaf wleaf[i] with targets
+// Leaf evaluation (M2P + P2P). Work item i is leaf wleaf[i] with targets
 // [tbeg + wt0[i], min(tbeg + wt0[i] + 64, tend)). Surface sources of a leaf are
-// the entries sbox/skind[soff[leaf] .. soff[leaf+1]) (kind 0: the downward
-// equivalent density phi_d of that box at radius rad_down, kind 1: the upward
-// density phi_u at radius rad_up, both times the box half-width and around
-// its centre; for the surface form 2.95 and 1.05, for the Chebyshev form
-// the node weights at the nodes, radius 1); point sources are the ranges
-// prng[poff[leaf] .. poff[leaf+1]). Results go to pot[r * n_trg + perm[k]] and
-// field[(r * n_trg + perm[k]) * 3 + c] (user order), overwriting (accumulate =
-// 0) or added to what is there (accumulate = 1).
+// the boxes sbox[soff[leaf] .. soff[leaf+1]): their upward density phi_u at
+// radius rad_up times the box half-width around its centre (the surface form's
+// equivalent density at 1.05, the Chebyshev form's node weights at the nodes,
+// radius 1); point sources are the ranges prng[poff[leaf] .. poff[leaf+1]).
+// Results go to pot[r * n_trg + perm[k]] and field[(r * n_trg + perm[k]) * 3 + c]
+// (user order), overwriting (accumulate = 0) or added to what is there
+// (accumulate = 1). The surface form's L2P (surface_to_points) takes the same
+// items: each leaf's own downward density phi_d at radius rad_down.
 constexpr int kEvalMaxWaves = 8;
 struct EvalArgs {
     const int32_t *wleaf = nullptr, *wt0 = nullptr;
     int nwork = 0;
     const int32_t *soff = nullptr, *sbox = nullptr;
-    const int8_t *skind = nullptr;
     const int32_t *poff = nullptr, *prng = nullptr;
     const int32_t *pmid = nullptr;  // per box: ranges [poff, pmid) need the r < delta test (NULL: all)
     const int64_t *tbeg = nullptr, *tend = nullptr;
@@ -55,13 +54,12 @@ struct EvalArgs {
     float delta2 = 0.f;
     float *pot = nullptr, *field = nullptr;
     int accumulate = 0;
-    int surf_mask = 3;  // surface kinds evaluated: bit 0 kind 0 (phi_d), bit 1 kind 1 (phi_u)
-    int points = 1;     // 0: skip the point ranges (surfaces only)
     int waves = 1;      // waves that share each work item's sources, 1..kEvalMaxWaves
     const int32_t *pcum = nullptr;  // per range: the sources in its leaf's ranges before it (waves > 1)
 };
 void eval_leaves(int nrhs, bool sl, bool dl, const EvalArgs &a, const SurfaceGeom &g, const PointSrc &src,
                  hipStream_t s);
+void surface_to_points(int nrhs, const EvalArgs &a, const SurfaceGeom &g, hipStream_t s);
 
 // All pairs, no tree: pot[i] = sum_j K(x_i, y_j), field likewise (nrhs = 1).
 void direct_all_pairs(const float *trg, int64_t n_trg, const float *src, const float *nrm, int64_t n_src,

@@ -973,7 +973,6 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
     std::vector<uint8_t> up_needed(nb, 0);
     std::vector<int32_t> wleaf, wt0, soff{0}, sbox, poff{0}, prng, pmid, pcum;
     std::vector<float> wcost;  // per work item, see below
-    std::vector<int8_t> skind;
     // Which point ranges need the r < delta test: tight bounding boxes of the
     // target points of every target leaf and of the source points of every
     // box that supplies points to one; a range is tested when it is the
@@ -1071,14 +1070,11 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
         if (lvl(b) >= 2) {
             down_boxes.push_back(b);
             if (!P.cheb) {  // the Chebyshev L2P is an interpolation (nodes_to_points), not a kernel sum
-                sbox.push_back(b);
-                skind.push_back(0);
                 P.surf_evals += ntrg(b) * ns;
             }
         }
         for (int32_t a : o.wsurf) {
             sbox.push_back(a);
-            skind.push_back(1);
             up_needed[a] = 1;
             P.surf_evals += ntrg(b) * ns;
         }
@@ -1139,7 +1135,6 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
     tr.up(P.wleaf, std::move(wleaf));
     tr.up(P.wt0, std::move(wt0));
     tr.up(P.sbox, std::move(sbox));
-    tr.up(P.skind, std::move(skind));
     prng.insert(prng.end(), 8, 0);  // the evaluation reads bounds up to 8 entries ahead
     tr.up(P.prng, std::move(prng));
     tr.up(P.pcum, std::move(pcum));
@@ -1328,7 +1323,6 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
     e.nwork = P.nwork;
     e.soff = P.soff.p;
     e.sbox = P.sbox.p;
-    e.skind = P.skind.p;
     e.poff = P.poff.p;
     e.prng = P.prng.p;
     e.pmid = P.pmid.p;
@@ -1361,9 +1355,7 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
         FMM_HIP(hipEventRecord(P.fork, s));
         FMM_HIP(hipStreamWaitEvent(P.side, P.fork, 0));
         if (ts) FMM_HIP(hipEventRecord(ts->side[2], P.side));
-        EvalArgs en = e;
-        if (!P.cheb) en.surf_mask = 2;  // M2P surfaces and the point ranges; L2P is a pass of its own
-        eval_leaves(nrhs, sl, dl, en, g, src, P.side);
+        eval_leaves(nrhs, sl, dl, e, g, src, P.side);
         if (ts) FMM_HIP(hipEventRecord(ts->side[3], P.side));
         FMM_HIP(hipEventRecord(P.join, P.side));
     };
@@ -1495,12 +1487,11 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
         run_gemm(P.c2e_down, op.cd_f64.p, np, rp, P.dt.p, P.phi_d.p, P.col_scale.p, false, s);
         FMM_HIP(hipStreamWaitEvent(s, P.join, 0));
         mark(ST_EVAL);
+        // L2P: each leaf's own downward surface, added to the near field
+        // (leaves above level 2 have none: their density stays zero)
         EvalArgs ef = e;
-        ef.surf_mask = 1;  // L2P: the leaf's own downward surface, added to the near field
-        ef.points = 0;
         ef.accumulate = 1;
-        ef.waves = 1;
-        eval_leaves(nrhs, sl, dl, ef, g, src, s);
+        surface_to_points(nrhs, ef, g, s);
     }
     mark(ST_COUNT);
     if (ts) ts->pending = true;

@@ -93,7 +93,6 @@ struct Plan {
     DBuf<int32_t> wleaf, wt0, soff, sbox, poff, prng;
     DBuf<int32_t> pmid;       // per box: its point ranges [poff, pmid) need the r < delta test
     int64_t p2p_tested = 0;   // target x source pairs in those ranges
-    DBuf<int8_t> skind;
     DBuf<int32_t> pcum;       // per range: sources in its leaf's ranges before it
     int nwork = 0;
     int eval_waves = 1;       // waves per work item of the evaluation
