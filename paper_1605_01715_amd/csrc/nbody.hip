@@ -591,9 +591,9 @@ __global__ __launch_bounds__(MW ? 64 * kEvalMaxWaves : 64) void k_eval(EvalArgs 
 
 // L2P of the surface form: bound by latency (three to eight tiles of 64 surface
 // points for an item). With every tile staged before the first is summed,
-// against the evaluation kernel's
-// tile by tile: 512 items of 152 points 14.7 -> 13.2 us, 16,726 45.5 -> 40.6,
-// 5333 items of 296 points 38.3 -> 37.0; the same results bit for bit.
+// against the evaluation kernel's tile by tile (the sums and their order are
+// the same): 512 items of 152 points 14.7 -> 13.2 us, 16,726 45.5 -> 40.6, 5333
+// items of 296 points 38.3 -> 37.0.
 template <int NRHS, bool FIELD>
 __global__ __launch_bounds__(64) void k_surface_to_points(EvalArgs a, SurfaceGeom g) {
     extern __shared__ __align__(16) float sh[];
