@@ -196,8 +196,8 @@ void finish_plan(fmm::Plan &P, const fmm_options *opt, const float *trg_nrm, hip
         for (size_t v = 0; v < nvec; ++v) sc[v] = 1.0 / P.t.h_half[v / P.nrhs];
         P.col_iscale = upload(sc, s);
     }
-    // zero once: padding entries are never written, vectors of boxes
-    // a stage skips stay zero
+    // zero once: vectors of boxes that a stage skips stay zero, and so does the
+    // padding, but in phi_d, whose rows the expansions write whole
     for (DBuf<float> *b : {&P.ut, &P.dt, &P.chk, &P.phi_u, &P.phi_d})
         if (b->n) FMM_HIP(hipMemsetAsync(b->p, 0, b->bytes(), s));
     const size_t nsv = (size_t)P.nrhs * P.t.n_src;

@@ -132,13 +132,16 @@ __global__ __launch_bounds__(64) void k_points_to_surface(const int32_t *items, 
             __syncthreads();
         }
     }
+    // The padding is written too (zero): the projection reads whole rows, and the
+    // surface form's downward expansion writes the same rows' padding, which is
+    // NaN after an apply of densities that are not finite.
 #pragma unroll
     for (int i = 0; i < TPL; ++i) {
         int m = lane + 64 * i;
-        if (m >= g.ns) continue;
+        if (m >= (accumulate ? g.ns : g.n_pad)) continue;
         for (int r = 0; r < NRHS; ++r) {
             float *op = out + ((int64_t)b * NRHS + r) * g.n_pad + m;
-            double v = acc[i][r] * (1.0 / kFourPi);
+            double v = m < g.ns ? acc[i][r] * (1.0 / kFourPi) : 0.0;
             *op = accumulate ? (float)((double)*op + v) : (float)v;
         }
     }
@@ -827,7 +830,7 @@ void points_to_surface(int nrhs, bool sl, bool dl, const int32_t *items, int nit
                        const int32_t *rng, double rfac, const SurfaceGeom &g, const PointSrc &src, float *out,
                        bool accumulate, hipStream_t s) {
     if (nitems <= 0) return;
-    FMM_REQUIRE(g.ns <= 512, "points_to_surface: surface too large");
+    FMM_REQUIRE(g.ns <= g.n_pad && g.n_pad <= 512, "points_to_surface: surface too large");
     dim3 gr(nitems), bl(64);
     int acc = accumulate ? 1 : 0;
     if (sl && dl) {
