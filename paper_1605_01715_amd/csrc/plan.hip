@@ -1137,6 +1137,7 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
     tr.up(P.sbox, std::move(sbox));
     prng.insert(prng.end(), 8, 0);  // the evaluation reads bounds up to 8 entries ahead
     tr.up(P.prng, std::move(prng));
+    pcum.push_back(0);  // an array also where no leaf has near points
     tr.up(P.pcum, std::move(pcum));
     {
         GemmJob &j = P.c2e_down;
