@@ -573,6 +573,8 @@ __device__ inline void eval_items(const EvalArgs &a, const SurfaceGeom &g, const
     using M = EvalLds<NRHS, SL, DL, FIELD>;
     constexpr int MAXTPL = M::MAXTPL;
     const int leaf = a.wleaf[blockIdx.x];
+    if constexpr (L2P)
+        if (a.level[leaf] < 2) return;
     const int64_t t_first = a.tbeg[leaf] + a.wt0[blockIdx.x];
     const int nt = (int)min((int64_t)64, a.tend[leaf] - t_first);
     const int best = targets_per_lane<MAXTPL>(nt);
@@ -849,6 +851,7 @@ void points_to_surface(int nrhs, bool sl, bool dl, const int32_t *items, int nit
 void surface_to_points(int nrhs, const EvalArgs &a, const SurfaceGeom &g, hipStream_t s) {
     if (a.nwork <= 0) return;
     FMM_REQUIRE(g.ns > 0 && g.ns <= 512 && g.n_pad >= g.ns, "surface_to_points: surface points");
+    FMM_REQUIRE(a.level, "surface_to_points: box levels");
     const int rec = (g.ns + 63) / 64 * 65;  // staged records
     const dim3 gr(a.nwork), bl(64);
 #define FMM_L2P_GO(FIELD)                                                                                        \

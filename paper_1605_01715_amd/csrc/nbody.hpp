@@ -37,7 +37,8 @@ void points_to_surface(int nrhs, bool sl, bool dl, const int32_t *items, int nit
 // Results go to pot[r * n_trg + perm[k]] and field[(r * n_trg + perm[k]) * 3 + c]
 // (user order), overwriting (accumulate = 0) or added to what is there
 // (accumulate = 1). The surface form's L2P (surface_to_points) takes the same
-// items: each leaf's own downward density phi_d at radius rad_down.
+// items: each leaf's own downward density phi_d at radius rad_down, for leaves
+// from level 2 on (those above have no far field).
 constexpr int kEvalMaxWaves = 8;
 struct EvalArgs {
     const int32_t *wleaf = nullptr, *wt0 = nullptr;
@@ -45,6 +46,7 @@ struct EvalArgs {
     const int32_t *soff = nullptr, *sbox = nullptr;
     const int32_t *poff = nullptr, *prng = nullptr;
     const int32_t *pmid = nullptr;  // per box: ranges [poff, pmid) need the r < delta test (NULL: all)
+    const int32_t *level = nullptr;  // per box (surface_to_points)
     const int64_t *tbeg = nullptr, *tend = nullptr;
     const float *tx = nullptr, *ty = nullptr, *tz = nullptr;
     const int64_t *trg_perm = nullptr;  // NULL: identity

@@ -1329,6 +1329,7 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
     e.pmid = P.pmid.p;
     e.pcum = P.pcum.p;
     e.waves = P.eval_waves;
+    e.level = t.level.p;
     e.tbeg = t.tbeg.p;
     e.tend = t.tend.p;
     if (t.tsm) {
@@ -1488,11 +1489,13 @@ void plan_apply(Plan &P, const float *q, const float *mu, float *pot, float *fie
         run_gemm(P.c2e_down, op.cd_f64.p, np, rp, P.dt.p, P.phi_d.p, P.col_scale.p, false, s);
         FMM_HIP(hipStreamWaitEvent(s, P.join, 0));
         mark(ST_EVAL);
-        // L2P: each leaf's own downward surface, added to the near field
-        // (leaves above level 2 have none: their density stays zero)
-        EvalArgs ef = e;
-        ef.accumulate = 1;
-        surface_to_points(nrhs, ef, g, s);
+        // L2P: each leaf's own downward surface, added to the near field (leaves
+        // above level 2 have none; on its points 1/r times a zero density is NaN)
+        if (P.c2e_down.ntile > 0) {
+            EvalArgs ef = e;
+            ef.accumulate = 1;
+            surface_to_points(nrhs, ef, g, s);
+        }
     }
     mark(ST_COUNT);
     if (ts) ts->pending = true;
