@@ -63,6 +63,7 @@ struct Block {
 void *device_malloc(size_t bytes);
 Block block_take(size_t bytes);      // at least `bytes`, on the current device
 void block_give(const Block &b);
+void block_free(const Block &b);      // past the pool
 void block_pool_tick();              // once per arena: ages the kept blocks
 
 // Device memory handed out from a few blocks: a plan makes some hundred
@@ -80,9 +81,15 @@ class Arena {
         int dev = blocks_[0].dev, cur = dev;
         (void)hipGetDevice(&cur);
         if (cur != dev) (void)hipSetDevice(dev);
-        (void)hipDeviceSynchronize();
+        const bool idle = hipDeviceSynchronize() == hipSuccess;
+        if (!idle) (void)hipGetLastError();
         if (cur != dev) (void)hipSetDevice(cur);
-        for (const Block &b : blocks_) block_give(b);
+        for (const Block &b : blocks_) {
+            if (idle)
+                block_give(b);
+            else
+                block_free(b);  // not waited for (a stream is being captured): left to hipFree's own wait
+        }
         block_pool_tick();
     }
     void *take(size_t bytes) {

@@ -103,6 +103,10 @@ void block_give(const Block &b) {
     (void)hipFree(b.p);
 }
 
+void block_free(const Block &b) {
+    if (hipFree(b.p) != hipSuccess) (void)hipGetLastError();
+}
+
 void block_pool_tick() {
     std::lock_guard<std::mutex> lk(g_pool_mu);
     for (Kept &k : pool()) ++k.age;

@@ -1,0 +1,110 @@
+// Host-side checks of the library's device-memory bookkeeping (Arena, the kept
+// blocks, Transfers) with the HIP calls it makes replaced by stand-ins over host
+// memory: allocations lie one directly after the other, a copy or a fill that
+// does not stay inside one allocation is refused, and the device-wide wait can
+// be made to fail as it does while a stream is being captured. Links against
+// the host side of primitives.hip. Exits non-zero on a failed expectation.
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <vector>
+
+#include "common.hpp"
+
+static int failures = 0;
+#define EXPECT(c)                                                         \
+    do {                                                                  \
+        if (!(c)) {                                                       \
+            std::fprintf(stderr, "failed: %s (line %d)\n", #c, __LINE__); \
+            ++failures;                                                   \
+        }                                                                 \
+    } while (0)
+
+// ------------------------------------------------------------ stand-ins
+static std::vector<char> g_mem(size_t(256) << 20);
+static size_t g_top = 0;                    // next free byte
+static std::map<char *, size_t> g_alloc;    // live allocations
+static int g_frees = 0, g_syncs = 0, g_copies = 0, g_fail_copy = 0;
+static hipError_t g_device_sync = hipSuccess;
+
+static bool inside_one(const void *p, size_t n) {
+    auto it = g_alloc.upper_bound((char *)p);
+    if (it == g_alloc.begin()) return false;
+    --it;
+    return (const char *)p + n <= it->first + it->second;
+}
+
+extern "C" {
+hipError_t hipMalloc(void **p, size_t n) {
+    if (g_top + n > g_mem.size()) return hipErrorOutOfMemory;
+    *p = g_mem.data() + g_top;
+    g_alloc[(char *)*p] = n;
+    g_top += n;
+    return hipSuccess;
+}
+hipError_t hipFree(void *p) {
+    ++g_frees;
+    g_alloc.erase((char *)p);
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind kind, hipStream_t) {
+    if (++g_copies == g_fail_copy) return hipErrorInvalidValue;
+    if (!inside_one(kind == hipMemcpyHostToDevice ? dst : src, n)) return hipErrorInvalidValue;
+    std::memcpy(dst, src, n);
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) {
+    ++g_syncs;
+    return hipSuccess;
+}
+hipError_t hipDeviceSynchronize() { return g_device_sync; }
+hipError_t hipGetDevice(int *d) {
+    *d = 0;
+    return hipSuccess;
+}
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return "refused"; }
+hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) { return hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3 *, dim3 *, size_t *, hipStream_t *) { return hipSuccess; }
+void **__hipRegisterFatBinary(const void *) { return nullptr; }
+void __hipRegisterFunction(void **, const void *, char *, const char *, unsigned, void *, void *, void *, void *, int *) {}
+void __hipUnregisterFatBinary(void **) {}
+}
+namespace fmm {
+bool inject_alloc_failure() { return false; }
+bool log_enabled() { return false; }
+void log_printf(const char *, ...) {}
+}  // namespace fmm
+
+using namespace fmm;
+
+// A block goes to the next arena only once nothing on the device uses it: with
+// the wait refused it is freed, which waits by itself.
+static void check_wait() {
+    void *first = nullptr;
+    {
+        Arena a;
+        first = a.take(1000);
+    }
+    EXPECT(g_frees == 0);
+    {
+        Arena a;
+        EXPECT(a.take(1000) == first);  // kept and handed out again
+        g_device_sync = hipErrorStreamCaptureUnsupported;
+    }
+    g_device_sync = hipSuccess;
+    EXPECT(g_frees == 1);
+    Arena a;
+    EXPECT(a.take(1000) != first);
+}
+
+int main(int argc, char **argv) {
+    const char *what = argc > 1 ? argv[1] : "";
+    if (!std::strcmp(what, "wait")) check_wait();
+    else return 2;
+    if (failures) return 1;
+    std::printf("memory checks passed: %s\n", what);
+    return 0;
+}
