@@ -97,7 +97,7 @@ class Arena {
         if (bytes > left_) {
             if (bytes >= next_) return block(bytes).p;  // its own block; the current one stays in use
             const Block b = block(next_);
-            cur_ = (char *)b.p;
+            begin_ = cur_ = (char *)b.p;
             left_ = b.bytes;
             if (next_ < kMaxBlock) next_ *= 2;
         }
@@ -106,12 +106,19 @@ class Arena {
         left_ -= bytes;
         return p;
     }
-    // the last piece taken can be taken again; others wait for the arena's end
+    // the current block's last piece can be taken again; others wait for the arena's
+    // end (another block may end where the current one begins)
     void give(void *p, size_t bytes) {
-        if ((char *)p + round(bytes) == cur_) {
+        if ((char *)p >= begin_ && (char *)p + round(bytes) == cur_) {
             cur_ -= round(bytes);
             left_ += round(bytes);
         }
+    }
+    // the start of the block that holds p
+    const char *block_of(const void *p) const {
+        for (const Block &b : blocks_)
+            if ((const char *)p >= (const char *)b.p && (const char *)p < (const char *)b.p + b.bytes) return (const char *)b.p;
+        return nullptr;
     }
 
   private:
@@ -123,7 +130,7 @@ class Arena {
         return blocks_.back();
     }
     std::vector<Block> blocks_;
-    char *cur_ = nullptr;
+    char *begin_ = nullptr, *cur_ = nullptr;  // the current block, its free part
     size_t left_ = 0, next_ = size_t(1) << 20;
 };
 
@@ -227,8 +234,8 @@ DBuf<T> upload(const std::vector<T> &v, hipStream_t s) {
 }
 
 // Copies of many small arrays in few calls. Arrays whose device buffers follow
-// each other (an arena hands them out in order) travel in one copy through a
-// host buffer, arrays of more than 1 MB by themselves; a setup has about 100 of
+// each other in one block (an arena hands them out in order) travel in one copy
+// through a host buffer, arrays of more than 1 MB by themselves; a setup has about 100 of
 // them, at some 30 us a call. flush() has finished when it returns.
 class Transfers {
   public:
@@ -238,13 +245,13 @@ class Transfers {
         dst.alloc(v.size());
         if (v.empty()) return;
         auto held = std::make_shared<std::vector<T>>(std::move(v));
-        items_.push_back({(char *)dst.p, (char *)held->data(), dst.bytes(), held});
+        items_.push_back({(char *)dst.p, (char *)held->data(), dst.bytes(), block(dst), held});
     }
     // h = the contents of src, filled by flush()
     template <class T>
     void down(std::vector<T> &h, const DBuf<T> &src, size_t count) {
         h.resize(count);
-        if (count) items_.push_back({(char *)src.p, (char *)h.data(), count * sizeof(T), nullptr});
+        if (count) items_.push_back({(char *)src.p, (char *)h.data(), count * sizeof(T), block(src), nullptr});
     }
     void flush_up(hipStream_t s) { flush(true, s); }
     void flush_down(hipStream_t s) { flush(false, s); }
@@ -253,8 +260,13 @@ class Transfers {
     struct Item {
         char *dev, *host;
         size_t bytes;
+        const char *block;  // a copy must not span two allocations, adjacent or not
         std::shared_ptr<void> held;
     };
+    template <class T>
+    static const char *block(const DBuf<T> &b) {
+        return b.home ? b.home->block_of(b.p) : (const char *)b.p;
+    }
     void flush(bool up, hipStream_t s);
     std::vector<Item> items_;
 };

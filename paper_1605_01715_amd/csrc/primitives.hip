@@ -287,7 +287,8 @@ void Transfers::flush(bool up, hipStream_t s) {
         size_t j = i + 1;
         const char *end = items_[i].dev + items_[i].bytes;
         // the next buffer starts within the padding of the last one's end
-        while (j < items_.size() && items_[j].bytes <= kLarge && items_[j].dev >= end && items_[j].dev - end < 256) {
+        while (j < items_.size() && items_[j].bytes <= kLarge && items_[j].block == items_[i].block &&
+               items_[j].dev >= end && items_[j].dev - end < 256) {
             end = items_[j].dev + items_[j].bytes;
             ++j;
         }

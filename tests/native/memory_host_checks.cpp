@@ -100,9 +100,48 @@ static void check_wait() {
     EXPECT(a.take(1000) != first);
 }
 
+// Pieces and copies stay inside one allocation also where the next one begins
+// right behind it.
+constexpr size_t MB = size_t(1) << 20;
+static void check_give() {
+    Arena a;
+    char *own = (char *)a.take(MB);  // a block of its own
+    char *p = (char *)a.take(256);   // the first piece of the block behind it
+    EXPECT(p == own + MB);
+    a.give(p, 256);
+    a.give(own, MB);  // not the current block's last piece
+    EXPECT(inside_one(a.take(MB + MB / 2), MB + MB / 2));
+}
+
+static void check_copies() {
+    Arena a;
+    ArenaScope scope(&a, &a);
+    Transfers tr;
+    DBuf<char> b[4];
+    std::vector<char> v[4] = {std::vector<char>(MB - 256, 'a'), std::vector<char>(256, 'b'),
+                              std::vector<char>(300, 'c'), std::vector<char>(200, 'd')};
+    for (int k = 0; k < 4; ++k) tr.up(b[k], v[k]);
+    EXPECT(b[2].p == b[1].p + 256 && b[3].p == b[2].p + 512);  // b[0], b[1] fill a block
+    try {
+        tr.flush_up(nullptr);
+        for (int k = 0; k < 4; ++k) EXPECT(std::memcmp(b[k].p, v[k].data(), v[k].size()) == 0);
+        std::vector<char> h[4];
+        for (int k = 0; k < 4; ++k) tr.down(h[k], b[k], v[k].size());
+        g_copies = 0;
+        tr.flush_down(nullptr);
+        EXPECT(g_copies == 2);
+        for (int k = 0; k < 4; ++k) EXPECT(h[k] == v[k]);
+    } catch (const Error &e) {
+        std::fprintf(stderr, "%s\n", e.what());
+        EXPECT(!"a copy left its allocation");
+    }
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "wait")) check_wait();
+    else if (!std::strcmp(what, "give")) check_give();
+    else if (!std::strcmp(what, "copies")) check_copies();
     else return 2;
     if (failures) return 1;
     std::printf("memory checks passed: %s\n", what);
