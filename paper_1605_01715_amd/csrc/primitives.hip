@@ -278,27 +278,33 @@ void Transfers::flush(bool up, hipStream_t s) {
         size_t first, last;  // items [first, last)
     };
     std::vector<Part> parts;
-    for (size_t i = 0; i < items_.size();) {
-        if (items_[i].bytes > kLarge) {
-            copy(items_[i].dev, items_[i].host, items_[i].bytes);
-            ++i;
-            continue;
+    try {
+        for (size_t i = 0; i < items_.size();) {
+            if (items_[i].bytes > kLarge) {
+                copy(items_[i].dev, items_[i].host, items_[i].bytes);
+                ++i;
+                continue;
+            }
+            size_t j = i + 1;
+            const char *end = items_[i].dev + items_[i].bytes;
+            // the next buffer starts within the padding of the last one's end
+            while (j < items_.size() && items_[j].bytes <= kLarge && items_[j].block == items_[i].block &&
+                   items_[j].dev >= end && items_[j].dev - end < 256) {
+                end = items_[j].dev + items_[j].bytes;
+                ++j;
+            }
+            held.emplace_back((size_t)(end - items_[i].dev));
+            char *h = held.back().data();
+            if (up)
+                for (size_t k = i; k < j; ++k)
+                    std::memcpy(h + (items_[k].dev - items_[i].dev), items_[k].host, items_[k].bytes);
+            copy(items_[i].dev, h, held.back().size());
+            if (!up) parts.push_back({held.size() - 1, i, j});
+            i = j;
         }
-        size_t j = i + 1;
-        const char *end = items_[i].dev + items_[i].bytes;
-        // the next buffer starts within the padding of the last one's end
-        while (j < items_.size() && items_[j].bytes <= kLarge && items_[j].block == items_[i].block &&
-               items_[j].dev >= end && items_[j].dev - end < 256) {
-            end = items_[j].dev + items_[j].bytes;
-            ++j;
-        }
-        held.emplace_back((size_t)(end - items_[i].dev));
-        char *h = held.back().data();
-        if (up)
-            for (size_t k = i; k < j; ++k) std::memcpy(h + (items_[k].dev - items_[i].dev), items_[k].host, items_[k].bytes);
-        copy(items_[i].dev, h, held.back().size());
-        if (!up) parts.push_back({held.size() - 1, i, j});
-        i = j;
+    } catch (...) {
+        (void)hipStreamSynchronize(s);  // the copies queued so far still use the host buffers
+        throw;
     }
     FMM_HIP(hipStreamSynchronize(s));
     for (const Part &p : parts)

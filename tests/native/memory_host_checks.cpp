@@ -137,11 +137,30 @@ static void check_copies() {
     }
 }
 
+// A copy that fails leaves no copy before it in flight: the stream is waited for
+// before the host buffers go.
+static void check_failed_copy() {
+    Arena a;
+    ArenaScope scope(&a, &a);
+    Transfers tr;
+    DBuf<char> b[3];
+    for (auto &x : b) tr.up(x, std::vector<char>(2 * MB, 'x'));
+    g_fail_copy = 3;
+    int code = FMM_OK;
+    try {
+        tr.flush_up(nullptr);
+    } catch (const Error &e) {
+        code = e.code;
+    }
+    EXPECT(code == FMM_ERR_DEVICE && g_copies == 3 && g_syncs == 1);
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "wait")) check_wait();
     else if (!std::strcmp(what, "give")) check_give();
     else if (!std::strcmp(what, "copies")) check_copies();
+    else if (!std::strcmp(what, "failed_copy")) check_failed_copy();
     else return 2;
     if (failures) return 1;
     std::printf("memory checks passed: %s\n", what);

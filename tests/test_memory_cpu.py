@@ -32,7 +32,7 @@ def checks(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["wait", "give", "copies"])
+@pytest.mark.parametrize("what", ["wait", "give", "copies", "failed_copy"])
 def test_memory_bookkeeping(checks, what):
     out = subprocess.run([checks, what], capture_output=True, text=True, timeout=60)
     assert out.returncode == 0, out.stdout + out.stderr
