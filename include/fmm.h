@@ -34,9 +34,11 @@
  *     ABI. On failure, fmm_last_error() returns a message describing it
  *     (thread-local, valid until the next call on the same thread).
  *   - Point arrays are float32, array-of-structures [n][3] (x, y, z).
- *   - Device memory of destroyed plans and finished solves is kept for the
- *     next ones, up to 512 MB a process; it is freed when the next eight do not
- *     use it, or when an allocation of the library fails.
+ *   - Device memory of destroyed plans and finished calls (solves, right-hand
+ *     sides, forces) is kept for the next ones, up to 512 MB a process; it is
+ *     freed once eight setups with their destroys, or sixteen such calls, have
+ *     passed without using it, when an allocation of the library fails, or by
+ *     fmm_release_memory.
  *
  * Environment variables read by the library:
  *   FMM_LOG            set (and not "0"): diagnostics on stderr
@@ -268,6 +270,10 @@ int fmm_body_forces(fmm_plan plan, const float *sigma_f, const float *sigma_b, c
  * A pointer the library never issued gives FMM_ERR_ARG. Destroying a plan
  * while another thread is inside a call on it is not allowed. */
 int fmm_destroy(fmm_plan plan);
+
+/* Frees the device memory kept from destroyed plans and finished calls. Any
+ * thread may call it at any time; plans and calls in progress are not touched. */
+int fmm_release_memory(void);
 
 /*
  * Leaf-size tuning by trial runs (the paper tunes its octree height per problem

@@ -19,7 +19,7 @@ from ._lib import (FMM_BASIS_CHEBYSHEV, FMM_BASIS_SURFACE, FMM_ERR_ARG, FMM_ERR_
                    FMM_OUT_POT, FMM_PREC_FP32, FMM_PREC_SPLIT_BF16, FMM_PREC_SPLIT_BF16X3, FMM_PREC_SPLIT_BF16X4,
                    FMM_SRC_DOUBLE, FMM_SRC_SINGLE, STAGES)
 
-__all__ = ["fmm_setup_batch", "Plan", "FmmError", "fmm_default_options", "fmm_setup", "fmm_apply", "gmres_solve", "fmm_destroy",
+__all__ = ["fmm_setup_batch", "Plan", "FmmError", "fmm_default_options", "fmm_setup", "fmm_apply", "gmres_solve", "fmm_destroy", "fmm_release_memory",
            "fmm_last_error", "fmm_direct", "fmm_plan_info", "fmm_export_tree", "fmm_export_stage",
            "fmm_set_timing", "fmm_set_graph", "fmm_dielectric_rhs", "fmm_body_forces", "fmm_stage_times", "fmm_pinv", "fmm_unit_surface", "fmm_split_bf16", "fmm_dielectric_rhs_noalloc", "fmm_autotune", "fmm_issue_probe",
            "library_path"]
@@ -168,6 +168,11 @@ def fmm_destroy(plan):
     h = plan.handle
     plan.handle = None
     _check(L.load().fmm_destroy(h))
+
+
+def fmm_release_memory():
+    """Frees the device memory kept from destroyed plans and finished calls."""
+    _check(L.load().fmm_release_memory())
 
 
 def fmm_direct(src_xyz, trg_xyz, q=None, mu=None, src_nrm=None, cutoff=1e-5, pot=None, field=None, stream=None):

@@ -71,6 +71,7 @@ SIGNATURES = {
     "gmres_solve": (c_int, [c_void_p, ctypes.POINTER(FmmOperator), c_void_p, c_void_p, c_double, c_int, c_int,
                             ctypes.POINTER(c_int), ctypes.POINTER(c_double), c_void_p]),
     "fmm_destroy": (c_int, [c_void_p]),
+    "fmm_release_memory": (c_int, []),
     "fmm_last_error": (ctypes.c_char_p, []),
     "fmm_direct": (c_int, [c_void_p, c_void_p, c_int64, c_void_p, c_int64, c_void_p, c_void_p, c_float, c_void_p,
                            c_void_p, c_void_p]),

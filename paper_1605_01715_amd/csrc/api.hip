@@ -429,6 +429,10 @@ int fmm_destroy(fmm_plan plan) {
     });
 }
 
+int fmm_release_memory(void) {
+    return guarded([] { fmm::block_pool_release(); });
+}
+
 int fmm_direct(const float *src_xyz, const float *src_nrm, int64_t n_src, const float *trg_xyz, int64_t n_trg,
                const float *q, const float *mu, float cutoff, float *pot, float *field, void *hip_stream) {
     return guarded([&] {

@@ -48,8 +48,10 @@ bool inject_alloc_failure();
 
 // Blocks of device memory between hipMalloc and the arenas below. A block
 // given back is kept for the next plan or solve, up to 512 MB a process (0.2%
-// of the GPU's memory); it is freed when it has not been taken again in the
-// next eight setups or solves, or when an allocation fails. hipMalloc and hipFree
+// of the GPU's memory); it is freed when it has not been taken again by the time
+// more than sixteen arenas have ended (a setup and its plan are two, a solve, a
+// right-hand side or a force call one), when an allocation fails, or on request
+// (fmm_release_memory). hipMalloc and hipFree
 // take about 1 us up to 1 MB, but in a program with several streams 40 and
 // 230-900 us for the blocks of a plan: 4.5 ms of the 16 ms that setting up,
 // applying once and destroying a 500,000-point plan took. Thread-safe;
@@ -65,6 +67,7 @@ Block block_take(size_t bytes);      // at least `bytes`, on the current device
 void block_give(const Block &b);
 void block_free(const Block &b);      // past the pool
 void block_pool_tick();              // once per arena: ages the kept blocks
+void block_pool_release();           // frees the kept blocks
 
 // Device memory handed out from a few blocks: a plan makes some hundred
 // buffers and as many temporaries. One thread uses an arena at a time; what is

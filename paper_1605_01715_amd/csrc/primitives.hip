@@ -17,7 +17,7 @@ struct Kept {
     int age = 0;  // arenas ended since it was given back
 };
 constexpr size_t kPoolBytes = size_t(512) << 20;
-constexpr int kPoolAge = 8;
+constexpr int kPoolAge = 16;
 std::mutex g_pool_mu;
 // never destroyed: the HIP runtime may be gone when static objects end
 std::vector<Kept> &pool() {
@@ -49,10 +49,7 @@ void *device_malloc(size_t bytes) {
     hipError_t e = hipMalloc(&p, bytes);
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
-        {
-            std::lock_guard<std::mutex> lk(g_pool_mu);
-            pool_drop([](const Kept &) { return true; });
-        }
+        block_pool_release();
         e = hipMalloc(&p, bytes);
     }
     if (e != hipSuccess) {
@@ -110,7 +107,12 @@ void block_free(const Block &b) {
 void block_pool_tick() {
     std::lock_guard<std::mutex> lk(g_pool_mu);
     for (Kept &k : pool()) ++k.age;
-    pool_drop([](const Kept &k) { return k.age > 2 * kPoolAge; });  // a setup ends two arenas
+    pool_drop([](const Kept &k) { return k.age > kPoolAge; });
+}
+
+void block_pool_release() {
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    pool_drop([](const Kept &) { return true; });
 }
 
 namespace {
