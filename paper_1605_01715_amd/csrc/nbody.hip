@@ -631,6 +631,75 @@ __global__ __launch_bounds__(64) void k_surface_to_points(EvalArgs a, SurfaceGeo
 // layer 3,720 -> 1,020 us.
 constexpr int kDirThreads = 1024;
 
+// one pair, as in k_direct below: v the source and its charge, m its dipole
+template <bool DL, bool FIELD, int NOUT>
+__device__ inline void direct_pair(float x, float y, float z, const float4 &v, const float4 &m, float delta2,
+                                   float (&part)[NOUT]) {
+    const float dx = x - v.x, dy = y - v.y, dz = z - v.z;
+    const float r2 = dx * dx + dy * dy + dz * dz;
+    float inv = rsq(r2);
+    inv = r2 < delta2 ? 0.f : inv;
+    const float inv2 = inv * inv;
+    if constexpr (FIELD) {
+        const float qi = v.w * inv, di3 = qi * inv2;
+        part[0] += qi;
+        part[1] += di3 * dx;
+        part[2] += di3 * dy;
+        part[3] += di3 * dz;
+    } else {
+        float w = v.w;
+        if (DL) w += (m.x * dx + m.y * dy + m.z * dz) * inv2;
+        part[0] += w * inv;
+    }
+}
+
+// Few sources: one thread per target, workgroups of 256, the sources staged 256
+// at a time. The slices of the kernel below cost a workgroup of 1024 threads and
+// two sums across it, which many targets with a few sources each do not repay.
+// 1M targets, 16 sources, single layer 44 -> 8 us (a launch), field 68 -> 11;
+// 10,000 targets, 64 sources, field 22 -> 8.
+template <bool DL, bool FIELD>
+__global__ __launch_bounds__(256) void k_direct_few(const float *trg, int64_t n_trg, const float *src,
+                                                   const float *nrm, int64_t n_src, const float *q, const float *mu,
+                                                   float delta2, float *pot, float *field) {
+    constexpr int NOUT = FIELD ? 4 : 1, TILE = 256;
+    __shared__ float4 a[TILE], b[DL ? TILE : 1];
+    const int t = threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * TILE + t, ic = min(i, n_trg - 1);
+    const float x = trg[3 * ic], y = trg[3 * ic + 1], z = trg[3 * ic + 2];
+    float hi[NOUT], lo[NOUT], part[NOUT];
+#pragma unroll
+    for (int o = 0; o < NOUT; ++o) hi[o] = lo[o] = 0.f;
+    for (int64_t j0 = 0; j0 < n_src; j0 += TILE) {
+        if (j0) __syncthreads();  // every wave is done with the tile before
+        const int cnt = (int)min((int64_t)TILE, n_src - j0);
+        if (t < cnt) {
+            const int64_t j = j0 + t;
+            float4 v = make_float4(src[3 * j], src[3 * j + 1], src[3 * j + 2], q ? q[j] : 0.f);
+            // a coordinate that is not finite makes every sum NaN, also where 1/r alone would give 0
+            v.w += 0.f * v.x + 0.f * v.y + 0.f * v.z;
+            a[t] = v;
+            if (DL) b[t] = make_float4(mu[j] * nrm[3 * j], mu[j] * nrm[3 * j + 1], mu[j] * nrm[3 * j + 2], 0.f);
+        }
+        __syncthreads();
+        for (int k0 = 0; k0 < cnt; k0 += 64) {  // float32 sums of at most 64 sources
+            const int k1 = min(cnt, k0 + 64);
+#pragma unroll
+            for (int o = 0; o < NOUT; ++o) part[o] = 0.f;
+#pragma unroll 4
+            for (int k = k0; k < k1; ++k) direct_pair<DL, FIELD>(x, y, z, a[k], DL ? b[k] : a[k], delta2, part);
+#pragma unroll
+            for (int o = 0; o < NOUT; ++o) two_sum_into(hi[o], lo[o], part[o]);
+        }
+    }
+    if (i >= n_trg) return;
+    const float nf = n_src > 0 ? 0.f * x + 0.f * y + 0.f * z : 0.f;  // as for the sources
+    if (pot) pot[i] = (hi[0] + lo[0]) * kInv4Pi + nf;
+    if (FIELD && field)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) field[3 * i + c] = (hi[NOUT - 3 + c] + lo[NOUT - 3 + c]) * kInv4Pi + nf;
+}
+
 template <bool DL, bool FIELD, int TPL, int KS>
 __global__ __launch_bounds__(kDirThreads) void k_direct(const float *trg, int64_t n_trg, const float *src,
                                                        const float *nrm, int64_t n_src, const float *q,
@@ -780,6 +849,13 @@ __global__ __launch_bounds__(kDirThreads) void k_direct(const float *trg, int64_
 template <bool DL, bool FIELD>
 void launch_direct(const float *trg, int64_t n_trg, const float *src, const float *nrm, int64_t n_src, const float *q,
                    const float *mu, float delta2, float *pot, float *field, hipStream_t s) {
+    const auto few = [&] {
+        hipLaunchKernelGGL((k_direct_few<DL, FIELD>), dim3((unsigned)((n_trg + 255) / 256)), dim3(256), 0, s, trg, n_trg,
+                           src, nrm, n_src, q, mu, delta2, pot, field);
+    };
+    // up to here a pass of k_direct_few ends within the launch's own 8 us
+    // (192 sources, field: 10.2 us, sliced 8.4)
+    if (n_src <= 128 && n_trg <= 65536) return few();
     // Targets per workgroup T = TPL << lg by a fit of the measured times: a
     // round of 256 workgroups (one per CU) costs T plus about 5.6 for staging
     // and latency, which two resident workgroups share. (300,000 sources,
@@ -788,20 +864,37 @@ void launch_direct(const float *trg, int64_t n_trg, const float *src, const floa
     // which only decide between splits of the same T; ties go to the larger T.
     constexpr int kTplMax = FIELD ? 2 : 4;
     int tpl = 1, lg = 0;
-    double best = 1e300;
-    for (int c = kTplMax; c >= 1; c >>= 1)
+    double best = 1e300, rounds_best = 0;
+    for (int c = kTplMax, lc = FIELD ? 1 : 2; c >= 1; c >>= 1, --lc)
         for (int l = 6; l >= 0; --l) {
             if (c > 1 && l < 2) continue;  // fewer than four lanes a slice: one target per lane instead
-            const int64_t T = (int64_t)c << l, wg = (n_trg + T - 1) / T;
-            const int64_t rounds = (wg + 255) / 256;
+            const int64_t T = (int64_t)c << l, wg = (n_trg + T - 1) >> (lc + l);
+            const int64_t rounds = (wg + 255) >> 8;
             const double cost = (double)rounds * (double)T * (c >= 4 ? 1.0 : c == 2 ? 1.02 : 1.05) +
                                 5.6 * (double)((rounds + 1) / 2);
             if (cost < best) {
                 best = cost;
+                rounds_best = (double)rounds;
                 tpl = c;
                 lg = l;
             }
         }
+    // One thread per target instead where that ends sooner. Sliced, a source
+    // costs 0.0587 ns per unit of the cost above (single layer), and each round
+    // its start and final sums; one thread per target, a source takes the chain
+    // of its pair, or, from three waves a SIMD, its issue. Microseconds, sliced
+    // and this: 1M targets and 64 sources 47 and 18 (field 81 and 27), 512
+    // sources 132 and 122, 100,000 targets and 256 sources 25 and 11 (field 42
+    // and 16), 1536 54 and 56. Each is off by up to 15% (200,000 targets, 1024
+    // sources: 61 and 70), hence the margin; with more than one of the sliced
+    // kernel's tiles its rounds overlap, and it is never far behind (1M targets,
+    // 2048 sources: 496 and 468; 100,000, field: 101 and 112).
+    constexpr double kPair = FIELD ? 1.43 : DL ? 1.4 : 1.0, kRound = FIELD ? 2.7 : DL ? 1.9 : 1.6;
+    constexpr double kChain = FIELD || DL ? 0.043 : 0.033, kIssue = FIELD ? 0.0235 : DL ? 0.022 : 0.0155;
+    const double waves = (double)((n_trg + 65535) / 65536);  // per SIMD
+    if (n_src <= 1024 && 1.15 * ((double)n_src * std::max(kChain, waves * kIssue) + 0.1 * waves) <=
+                             (double)n_src * 5.87e-5 * kPair * best + kRound * rounds_best)
+        return few();
     const int64_t T = (int64_t)tpl << lg;
     const dim3 g((unsigned)((n_trg + T - 1) / T)), b(kDirThreads);
     auto go = [&](auto kern) {
