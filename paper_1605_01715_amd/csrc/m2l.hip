@@ -131,8 +131,12 @@ struct Shape {
     static_assert(kCols * SPC % 64 == 0, "B slots must fill whole copies");
 };
 
+// Waves per SIMD that the registers leave room for: in float32 up to 256 rows
+// four, two workgroups (left to itself the compiler takes 130 registers at 256
+// rows, room for one: 41,560 targets of 124,679 sources, leaves of 16, four
+// densities 24.4 ms, 21.7 with two; the field of 56,084 points 3.64 and 2.82).
 template <int NRB, int FORM, int NW, bool LEAN>
-__global__ __launch_bounds__(NW * 64, LEAN ? 6 : 2) void k_m2l(M2LLaunch a) {
+__global__ __launch_bounds__(NW * 64, LEAN ? 6 : FORM == 0 && NRB <= 8 ? 4 : 2) void k_m2l(M2LLaunch a) {
     using S = Shape<NRB, FORM, NW>;
     constexpr bool BF16 = S::BF16;
     constexpr int NP = S::NP;

@@ -559,6 +559,7 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             const double s45 = span_at(0.45, n45), s65 = span_at(0.65, n65);
             if (s65 < 0.97 * s45 && n65 * nc * P.r_pad * (int64_t)sizeof(float) <= (int64_t)4 << 30) pair_fill = 0.65;
         }
+        P.m2l_fill = pair_fill;
         std::vector<uint8_t> pair_tile(ntile, 0);
         {
             // the columns of the sparse tiles
@@ -658,6 +659,7 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
                         }
                     }
                 }
+                P.m2l_group = G;
                 if (G != 4) count(G);
                 // a counting sort over the classes of the targets taken in
                 // increasing order, in parallel over chunks of the targets
@@ -763,6 +765,7 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             P.eval_after_m2l = (P.m2l_form == 0 || P.m2l_form == 6) && P.r_pad >= 96 && b.load >= 3.0 && b.load >= b.chain;
             lap("m2l pair tiles and piece model");
             P.m2l_pieces_per_tile = kbest;
+            P.m2l_blocks = slots / 32;
             // pieces: (tile, first direction, last direction + 1, partial slot or -1)
             struct Piece {
                 int tile, e0, e1, slot;
@@ -1208,6 +1211,9 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
     }
     tr.flush_up(s);
     wl("evaluation uploads, expansion and Chebyshev lists");
+    FMM_LOG("choices: rows=%d blocks=%d lean=%d fill=%.2f pair_tiles=%d group=%d pieces=%d eval_after=%d eval_waves=%d\n",
+            P.r_pad, P.m2l_blocks, (int)P.m2l_lean, P.m2l_fill, P.m2l_pair_tiles, P.m2l_group, P.m2l_pieces_per_tile,
+            (int)P.eval_after_m2l, P.eval_waves);
     phase_end(6);
 }
 

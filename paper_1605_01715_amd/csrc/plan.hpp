@@ -84,6 +84,8 @@ struct Plan {
     DBuf<int32_t> m2l_slot;  // per work item: partial-sum slot, or -1 (adds into dt)
     bool m2l_lean = false;        // M2LLaunch::lean
     bool eval_after_m2l = false;  // the leaf evaluation's fork: before or after the M2L kernel
+    int m2l_blocks = 0, m2l_group = 1;  // workgroups a CU the schedule counts on; directions grouped in pair tiles
+    double m2l_fill = 0.0;        // tiles filled less become pair tiles
     int m2l_nsplit = 0, m2l_pieces_per_tile = 1;  // tiles cut into pieces; pieces per cut tile
     DBuf<float> m2l_partial;                      // [slot][ncol][r_pad] partial sums of cut tiles
     DBuf<int32_t> m2l_red_cols, m2l_red_slot0, m2l_red_k;  // per cut tile: columns, first slot, pieces
