@@ -29,14 +29,19 @@ namespace fmm {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kWaves = kBlock / 64;
+constexpr int kBigBlock = 1024;
 constexpr int kDots = 4;         // dot products accumulated at once
 constexpr int kCoefArg = 64;     // update coefficients passed as a kernel argument
 
-// Blocks that share a vector: one element a thread up to 65,536 points, then
-// 512 blocks (each of which reads all blocks' sums).
+// Blocks that share a vector, at most 512, as each of them reads all blocks'
+// sums: of 256 threads while that is one element a thread, then of 1024, with
+// which more of the vectors is in flight. Per step beyond the apply, blocks of
+// 256 and 1024: 196,000 points, 60 vectors 134 and 107 us (separate kernels 128);
+// 1M points, 30 vectors 178 and 151 (194), 60 vectors 318 and 255 (269).
+int vec_threads(int64_t n) { return n <= 512 * kBlock ? kBlock : kBigBlock; }
 int vec_blocks(int64_t n) {
-    return (int)std::max<int64_t>(1, std::min<int64_t>(n <= 65536 ? 256 : 512, (n + kBlock - 1) / kBlock));
+    const int64_t t = vec_threads(n);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(n <= 65536 ? 256 : 512, (n + t - 1) / t));
 }
 
 __device__ inline double wave_sum(double v) {
@@ -48,13 +53,14 @@ __device__ inline double wave_sum(double v) {
 // partial[k * gridDim.x + block] = this block's share of V_k . y, k < nk
 // (V NULL: y . y, nk = 1); each thread reads back only elements it wrote.
 __device__ inline void block_dots(const double *V, int64_t ldv, int nk, const double *y, int64_t n, double *partial) {
-    __shared__ double sh[kWaves][kDots];
+    __shared__ double sh[kBigBlock / 64][kDots];
+    const int waves = blockDim.x >> 6;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     for (int k0 = 0; k0 < nk; k0 += kDots) {
         double acc[kDots];
 #pragma unroll
         for (int j = 0; j < kDots; ++j) acc[j] = 0.0;
-        for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
+        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
             const double yi = y[i];
 #pragma unroll
             for (int j = 0; j < kDots; ++j)
@@ -69,7 +75,7 @@ __device__ inline void block_dots(const double *V, int64_t ldv, int nk, const do
         __syncthreads();
         if (threadIdx.x < kDots && k0 + threadIdx.x < nk) {
             double v = sh[0][threadIdx.x];
-            for (int q = 1; q < kWaves; ++q) v += sh[q][threadIdx.x];
+            for (int q = 1; q < waves; ++q) v += sh[q][threadIdx.x];
             partial[(int64_t)(k0 + threadIdx.x) * gridDim.x + blockIdx.x] = v;
         }
     }
@@ -78,7 +84,7 @@ __device__ inline void block_dots(const double *V, int64_t ldv, int nk, const do
 // h[k] (LDS) = sum over the blocks of partial[k], k < nk
 __device__ inline void sum_partials(const double *partial, int nk, double *h) {
     const int lane = threadIdx.x & 63;
-    for (int k = threadIdx.x >> 6; k < nk; k += kWaves) {
+    for (int k = threadIdx.x >> 6; k < nk; k += (int)(blockDim.x >> 6)) {
         double v = 0.0;
         for (int b = lane; b < (int)gridDim.x; b += 64) v += partial[(int64_t)k * gridDim.x + b];
         v = wave_sum(v);
@@ -96,11 +102,11 @@ __global__ void k_density(const double *x, const float *w, float *dens, int64_t 
 // y = a x + c (field . n)            (dielectric)
 // and, with b given, y = b - that (the residual). Block sums: V_k . y for k < nk,
 // or (b given) y . y in partial[0] and b . b in partial[1].
-__global__ __launch_bounds__(kBlock) void k_operator(int kind, const double *x, const float *a, const float *c,
+__global__ __launch_bounds__(kBigBlock) void k_operator(int kind, const double *x, const float *a, const float *c,
                                                      const float *pot, const float *field, const float *nrm,
                                                      const double *b, double *y, int64_t n, const double *V,
                                                      int64_t ldv, int nk, double *partial) {
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         double v = (double)a[i] * x[i];
         if (kind == FMM_OP_FK) {
             v += (double)pot[i];
@@ -122,13 +128,13 @@ __global__ __launch_bounds__(kBlock) void k_operator(int kind, const double *x, 
 // One Gram-Schmidt pass: h_k = the block sums `in`, w -= sum_k h_k V_k, block
 // sums of the new V_k . w (last = 0) or of w . w (last = 1) to `out`; block 0
 // keeps the coefficients in hdev.
-__global__ __launch_bounds__(kBlock) void k_orthogonal(const double *V, int64_t ldv, int nk, const double *in, double *w,
+__global__ __launch_bounds__(kBigBlock) void k_orthogonal(const double *V, int64_t ldv, int nk, const double *in, double *w,
                                                        int64_t n, double *hdev, double *out, int last) {
     extern __shared__ double h[];
     sum_partials(in, nk, h);
     if (blockIdx.x == 0)
-        for (int k = threadIdx.x; k < nk; k += kBlock) hdev[k] = h[k];
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
+        for (int k = threadIdx.x; k < nk; k += blockDim.x) hdev[k] = h[k];
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         double acc = w[i];
         for (int k = 0; k < nk; ++k) acc -= h[k] * V[(int64_t)k * ldv + i];
         w[i] = acc;
@@ -140,20 +146,20 @@ __global__ __launch_bounds__(kBlock) void k_orthogonal(const double *V, int64_t 
 // breakdown: v = w), and dens = v wgt. Block 0 hands the host the coefficients
 // of both passes (nk each; h2 after stride doubles) and, from index 2 stride,
 // the nsum sums of `in`. w and v may be the same.
-__global__ __launch_bounds__(kBlock) void k_normalise(const double *w, double *v, const double *in, int nsum,
+__global__ __launch_bounds__(kBigBlock) void k_normalise(const double *w, double *v, const double *in, int nsum,
                                                       double floor, const float *wgt, float *dens, int64_t n,
                                                       const double *hdev, int nk, int stride, double *host) {
     __shared__ double sum[2];
     sum_partials(in, nsum, sum);
     const double nrm = sqrt(sum[0]);
     const bool keep = nrm <= floor;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const double x = keep ? w[i] : w[i] / nrm;
         v[i] = x;
         dens[i] = (float)(x * (double)wgt[i]);
     }
     if (blockIdx.x == 0) {
-        for (int k = threadIdx.x; k < nk; k += kBlock) {
+        for (int k = threadIdx.x; k < nk; k += blockDim.x) {
             host[k] = hdev[k];
             host[stride + k] = hdev[stride + k];
         }
@@ -212,12 +218,12 @@ struct Gmres {
     }
     void oper(const double *x, const double *b, double *y, const double *V, int64_t ldv, int nk) {
         apply();
-        hipLaunchKernelGGL(k_operator, dim3(nb), dim3(kBlock), 0, s, op.kind, x, op.a, op.c, pot.p, field.p,
+        hipLaunchKernelGGL(k_operator, dim3(nb), dim3(vec_threads(n)), 0, s, op.kind, x, op.a, op.c, pot.p, field.p,
                            P.trg_nrm_user.p, b, y, n, V, ldv, nk, pa.p);
         FMM_HIP(hipGetLastError());
     }
     void normalise(const double *w, double *v, const double *sums, int nsum, double floor, int nk) {
-        hipLaunchKernelGGL(k_normalise, dim3(nb), dim3(kBlock), 0, s, w, v, sums, nsum, floor, op.w, dens.p, n, hdev.p,
+        hipLaunchKernelGGL(k_normalise, dim3(nb), dim3(vec_threads(n)), 0, s, w, v, sums, nsum, floor, op.w, dens.p, n, hdev.p,
                            nk, kmax, host);
         FMM_HIP(hipGetLastError());
         FMM_HIP(hipStreamSynchronize(s));  // the host reads the coefficients
@@ -239,9 +245,9 @@ struct Gmres {
         if (nk > kmax) throw Error(FMM_ERR_ARG, "gmres: more Krylov vectors than the restart length");
         oper(V + (int64_t)(nk - 1) * ldv, nullptr, w, V, ldv, nk);
         const size_t sh = (size_t)nk * sizeof(double);
-        hipLaunchKernelGGL(k_orthogonal, dim3(nb), dim3(kBlock), sh, s, V, ldv, nk, pa.p, w, n, hdev.p, pb.p, 0);
+        hipLaunchKernelGGL(k_orthogonal, dim3(nb), dim3(vec_threads(n)), sh, s, V, ldv, nk, pa.p, w, n, hdev.p, pb.p, 0);
         FMM_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_orthogonal, dim3(nb), dim3(kBlock), sh, s, V, ldv, nk, pb.p, w, n, hdev.p + kmax, pa.p, 1);
+        hipLaunchKernelGGL(k_orthogonal, dim3(nb), dim3(vec_threads(n)), sh, s, V, ldv, nk, pb.p, w, n, hdev.p + kmax, pa.p, 1);
         FMM_HIP(hipGetLastError());
         normalise(w, w, pa.p, 1, floor, nk);
         for (int i = 0; i < nk; ++i) h[i] = host[i] + host[kmax + i];
