@@ -243,6 +243,16 @@ void merge_ranges(std::vector<int32_t> &r, size_t from) {
 // 40 spheres with the field, 3.5: 220 -> 134 us with 4; a body of 14,700
 // points, 5.3: 59 -> 25 us with 4; 5762 nodes of a surface under 80,640
 // sources, 4.0: 167 -> 61 us with 4.
+// That count goes by the longest item alone. It is replaced by the count with the
+// least estimated time where that is a quarter less: the work, with what each wave
+// costs beside its sources (its start about 30 sources, each of its sums 15, in
+// sources of one density), over the SIMDs, plus the longest wave. One wave where
+// items are many and short (31,932 items of 8 targets, field of three densities,
+// apply: one wave 1387 us, two 1598, four 1976), more where there are few for
+// each SIMD, whose numbers then differ by a third or more, most of all beside M2L
+// workgroups on some of the CUs (200,576 points in 512 leaves, 3.5 items: one
+// wave 1342 us, four 713). Over 215 plans of 2000 to 600,000 points this was 4%
+// slower than the best count on average, the longest item alone 6%, one wave 40%.
 //
 // Where more than one is needed, the items of more than eight, four and two
 // times the mean cost also start first. Otherwise the items keep the leaves'
@@ -257,6 +267,12 @@ void order_eval_items(Plan &P, std::vector<int32_t> &wleaf, std::vector<int32_t>
         top = std::max(top, (double)c);
     }
     while (P.eval_waves < kEvalMaxWaves && top > std::max(1.35 * sum / 1024.0, 128.0) * P.eval_waves) P.eval_waves *= 2;
+    const double own = (30.0 + 15.0 * P.nrhs * (P.want_field ? 4 : 1)) / P.nrhs;
+    auto time = [&](int w) { return (sum + own * (double)n * w) / 1024.0 + top / w; };
+    int best = 1;
+    for (int w = 2; w <= kEvalMaxWaves && top > 64.0 * w; w *= 2)
+        if (time(w) < time(best)) best = w;
+    if (time(best) < 0.75 * time(P.eval_waves)) P.eval_waves = best;
     if (P.eval_waves == 1) return;
     const double mean = sum / (double)n;
     auto rank_of = [&](float c) { return c > 8 * mean ? 0 : c > 4 * mean ? 1 : c > 2 * mean ? 2 : 3; };

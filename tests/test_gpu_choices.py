@@ -1,5 +1,5 @@
 """Which of a setup's ways each kind of plan takes (the FMM_LOG line "choices"):
-the M2L kernel's workgroups a CU. The accuracy on each of them is tested
+the M2L kernel's workgroups a CU, the evaluation's waves an item. The accuracy on each of them is tested
 elsewhere; here a changed rule or kernel that no longer reaches one shows."""
 
 import json
@@ -17,6 +17,9 @@ pytestmark = pytest.mark.gpu
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 PLANS = {
+    "few_big_leaves": dict(shape="cube", n=200_576, order=7, basis=1, precision=2, leaf=400),
+    "many_short_items": dict(shape="line", n=267_667, order=6, basis=1, precision=1, nrhs=3, outputs=2, leaf=16),
+    "few_points": dict(shape="cube", n=100, order=4, leaf=64),
     "order10": dict(shape="cube", n=3000, order=10, eps=1e-8, leaf=64),
 }
 
@@ -33,6 +36,9 @@ for name, c in json.loads(sys.argv[1]).items():
         x /= np.linalg.norm(x, axis=1, keepdims=True)
     elif c["shape"] == "cloud":
         x = W.clustered(n, seed=1)["xyz"]
+    elif c["shape"] == "line":
+        t = rng.random(n)
+        x = np.stack([t, t * t, 0.3 + 0.1 * t], 1)
     else:
         x = rng.random((n, 3))
     o = F.fmm_default_options(order=c["order"], basis=c.get("basis", 0), leaf_size=c["leaf"], pinv_eps=c.get("eps", 0.0),
@@ -63,3 +69,9 @@ def choices():
 
 def test_two_workgroups_a_cu_at_256_rows(choices):
     assert choices["order10"]["rows"] == 256 and choices["order10"]["blocks"] >= 2
+
+
+def test_evaluation_waves(choices):
+    assert choices["few_big_leaves"]["eval_waves"] >= 4  # 3.5 items for each SIMD
+    assert choices["many_short_items"]["eval_waves"] == 1
+    assert choices["few_points"]["eval_waves"] == 1
