@@ -766,19 +766,22 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
                 kbest = best_pieces(nd);
                 b = bound(nd, kbest);
             }
-            // Float32 and bf16x6 translations that keep every CU busy for three
-            // steps or more, and longer than their longest piece, are bound by
+            // Float32 and bf16x6 translations that keep every CU busy for five
+            // steps or more, and for twice their longest piece, are bound by
             // the matrix cores: a leaf evaluation beside them delays them by
             // what it takes, but one launched after them fills the gaps of the
-            // reduction, the gather and the downward pass. After instead of beside:
-            // 300,000-point cloud, order 8, bf16x6 1600 -> 1448 us; eight
-            // spheres 690 -> 684; uniform 400,000, order 6 3275 -> 3071. Where
-            // CUs run out of tiles the evaluation is welcome beside them (4096
-            // points 134 us, after 138; cloud of 200,000, order 6 1116,
-            // 1198), as it is beside the shorter bf16x3 steps that wait on
-            // memory (field of 300 spheres 617, 822) and those of matrices
-            // below 96 rows (order 4, 100,000 points 313, 383).
-            P.eval_after_m2l = (P.m2l_form == 0 || P.m2l_form == 6) && P.r_pad >= 96 && b.load >= 3.0 && b.load >= b.chain;
+            // reduction, the gather and the downward pass. Beside and after:
+            // 120,000-point cloud, order 8 2870 and 2542 us (load 112, longest
+            // piece 50); 24,900, order 5 230 and 211 (9.8, 3.5); eight spheres
+            // 671 and 642 (7.5, 2.9). Below twice the piece CUs run out of
+            // tiles while it ends and the evaluation is welcome beside them:
+            // cloud of 294,317, order 5, field 1073 and 1203 (91, 59); of
+            // 220,247, order 6, field of four densities in bf16x6 2130 and
+            // 2398 (24, 21); 475,258, field 1503 and 1641 (62, 54). As it is
+            // beside the shorter bf16x3 steps that wait on memory (field of 300
+            // spheres 548, 708; 4M points 7563, 8070) and those of matrices
+            // below 96 rows (order 4, 31,369 points 342, 374).
+            P.eval_after_m2l = (P.m2l_form == 0 || P.m2l_form == 6) && P.r_pad >= 96 && b.load >= 5.0 && b.load >= 2.0 * b.chain;
             lap("m2l pair tiles and piece model");
             P.m2l_pieces_per_tile = kbest;
             P.m2l_blocks = slots / 32;
