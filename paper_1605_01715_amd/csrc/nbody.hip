@@ -961,6 +961,20 @@ void surface_to_points(int nrhs, const EvalArgs &a, const SurfaceGeom &g, hipStr
     FMM_HIP(hipGetLastError());
 }
 
+size_t eval_wave_lds(int nrhs, bool sl, bool dl, bool field) {
+    size_t floats = 0;
+    if (field) {
+        FMM_NRHS_SWITCH(nrhs, (floats = EvalLds<R, true, false, true>::N));
+    } else if (sl && dl) {
+        FMM_NRHS_SWITCH(nrhs, (floats = EvalLds<R, true, true, false>::N));
+    } else if (dl) {
+        FMM_NRHS_SWITCH(nrhs, (floats = EvalLds<R, false, true, false>::N));
+    } else {
+        FMM_NRHS_SWITCH(nrhs, (floats = EvalLds<R, true, false, false>::N));
+    }
+    return floats * sizeof(float);
+}
+
 void eval_leaves(int nrhs, bool sl, bool dl, const EvalArgs &a, const SurfaceGeom &g, const PointSrc &src,
                  hipStream_t s) {
     if (a.nwork <= 0) return;

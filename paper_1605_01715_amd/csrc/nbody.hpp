@@ -61,6 +61,8 @@ struct EvalArgs {
 };
 void eval_leaves(int nrhs, bool sl, bool dl, const EvalArgs &a, const SurfaceGeom &g, const PointSrc &src,
                  hipStream_t s);
+// LDS bytes of each wave of eval_leaves
+size_t eval_wave_lds(int nrhs, bool sl, bool dl, bool field);
 void surface_to_points(int nrhs, const EvalArgs &a, const SurfaceGeom &g, hipStream_t s);
 
 // All pairs, no tree: pot[i] = sum_j K(x_i, y_j), field likewise (nrhs = 1).

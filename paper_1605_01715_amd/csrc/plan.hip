@@ -28,6 +28,7 @@ namespace fmm {
 namespace {
 
 constexpr int kBlock = 256;
+constexpr size_t kLdsPerCu = 160 * 1024;
 
 // plain fill (a memset node does not replay reliably inside captured graphs)
 // Tight bounding boxes of the points of listed boxes: one wave per box,
@@ -243,16 +244,19 @@ void merge_ranges(std::vector<int32_t> &r, size_t from) {
 // 40 spheres with the field, 3.5: 220 -> 134 us with 4; a body of 14,700
 // points, 5.3: 59 -> 25 us with 4; 5762 nodes of a surface under 80,640
 // sources, 4.0: 167 -> 61 us with 4.
-// That count goes by the longest item alone. It is replaced by the count with the
-// least estimated time where that is a quarter less: the work, with what each wave
-// costs beside its sources (its start about 30 sources, each of its sums 15, in
-// sources of one density), over the SIMDs, plus the longest wave. One wave where
-// items are many and short (31,932 items of 8 targets, field of three densities,
-// apply: one wave 1387 us, two 1598, four 1976), more where there are few for
-// each SIMD, whose numbers then differ by a third or more, most of all beside M2L
-// workgroups on some of the CUs (200,576 points in 512 leaves, 3.5 items: one
-// wave 1342 us, four 713). Over 215 plans of 2000 to 600,000 points this was 4%
-// slower than the best count on average, the longest item alone 6%, one wave 40%.
+// That count goes by the longest item alone. It gives way to the count with the
+// least estimated time where that is a fifth less, or a tenth with fewer waves:
+// the work, with what each wave costs beside its sources (its start 30 sources,
+// each of its sums 20, of one density; per density they share), over the SIMDs,
+// slower where the waves' LDS leaves fewer than 12 of them on a CU, plus the
+// longest wave. One wave where items are many and short (31,932 items of 8
+// targets, field of three densities, apply: one wave 1387 us, two 1598, four
+// 1976), more where there are few for each SIMD, whose numbers then differ by a
+// third or more, most of all beside M2L workgroups on some of the CUs (200,576
+// points in 512 leaves, 3.5 items: one wave 1342 us, four 713), fewer where eight
+// take the LDS of a CU (field of four densities, 1638 items: four 454, eight 552).
+// Over 340 plans of 2000 to 600,000 points this was 2.9% slower than the best
+// count on average, the longest item alone 5.7%.
 //
 // Where more than one is needed, the items of more than eight, four and two
 // times the mean cost also start first. Otherwise the items keep the leaves'
@@ -267,12 +271,16 @@ void order_eval_items(Plan &P, std::vector<int32_t> &wleaf, std::vector<int32_t>
         top = std::max(top, (double)c);
     }
     while (P.eval_waves < kEvalMaxWaves && top > std::max(1.35 * sum / 1024.0, 128.0) * P.eval_waves) P.eval_waves *= 2;
-    const double own = (30.0 + 15.0 * P.nrhs * (P.want_field ? 4 : 1)) / P.nrhs;
-    auto time = [&](int w) { return (sum + own * (double)n * w) / 1024.0 + top / w; };
+    const double own = (30.0 + 20.0 * P.nrhs * (P.want_field ? 4 : 1)) / std::sqrt((double)P.nrhs);
+    const size_t lds = eval_wave_lds(P.nrhs, P.sl, P.dl, P.want_field);
+    auto time = [&](int w) {
+        const double on_cu = (double)(kLdsPerCu / (lds * w) * w);
+        return (sum + own * (double)n * w) / 1024.0 * std::max(1.0, 12.0 / on_cu) + top / w;
+    };
     int best = 1;
     for (int w = 2; w <= kEvalMaxWaves && top > 64.0 * w; w *= 2)
         if (time(w) < time(best)) best = w;
-    if (time(best) < 0.75 * time(P.eval_waves)) P.eval_waves = best;
+    if (time(best) < (best > P.eval_waves ? 0.8 : 0.9) * time(P.eval_waves)) P.eval_waves = best;
     if (P.eval_waves == 1) return;
     const double mean = sum / (double)n;
     auto rank_of = [&](float c) { return c > 8 * mean ? 0 : c > 4 * mean ? 1 : c > 2 * mean ? 2 : 3; };
