@@ -169,7 +169,11 @@ __global__ __launch_bounds__(64) void k_points_to_nodes(const double *coef, cons
 // sources in sequence); with more leaves the staging's barriers and the final
 // sums cost more than they save. Measured, one wave -> four: 224 leaves, double
 // layer, n = 8 20 -> 11.5 us; 6953 leaves 28 -> 35 us; 77,834 leaves 502 -> 634
-// us.
+// us. About the line of 1024 leaves it depends on their points (n = 8, single
+// layer; both layers and four densities): 512 leaves of 39 points 10.1 -> 9.8 and
+// 23.8 -> 16.7 us, of 11 points 8.9 -> 8.1 and 14.6 -> 13.2; 1100 of 93 30.7 -> 17.3
+// and 93 -> 51; 1480 of 8 9.3 -> 11.0 and 15.2 -> 22.2; 3800 of 26 16.8 -> 21.2 and
+// 46.7 -> 54.5.
 template <int N, int NRHS, bool SL, bool DL>
 __global__ __launch_bounds__(256) void k_points_to_nodes4(const double *coef, const int32_t *items,
                                                          const int32_t *roff, const int32_t *rng, SurfaceGeom g,
@@ -227,8 +231,8 @@ __global__ __launch_bounds__(256) void k_points_to_nodes4(const double *coef, co
                 pair_to_nodes<N, NRHS, SL, DL, W, OS, OD, OQ, OM>(sh + jj * W, jy, kz, acc);
         }
     }
-#pragma unroll 1
-    for (int r = 0; r < NRHS; ++r) {
+#pragma unroll
+    for (int r = 0; r < NRHS; ++r) {  // static index keeps acc in registers
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < N; ++i) red[(w * N + i) * 64 + lane] = acc[i][r];
