@@ -785,10 +785,13 @@ void plan_build_worklists(Plan &P, hipStream_t s) {
             // tiles while it ends and the evaluation is welcome beside them:
             // cloud of 294,317, order 5, field 1073 and 1203 (91, 59); of
             // 220,247, order 6, field of four densities in bf16x6 2130 and
-            // 2398 (24, 21); 475,258, field 1503 and 1641 (62, 54). As it is
-            // beside the shorter bf16x3 steps that wait on memory (field of 300
-            // spheres 548, 708; 4M points 7563, 8070) and those of matrices
-            // below 96 rows (order 4, 31,369 points 342, 374).
+            // 2398 (24, 21); 475,258, field 1503 and 1641 (62, 54). It stays
+            // beside bf16x3 steps too, on balance: of 117 such plans 70 are
+            // faster by more than 2% beside and 11 after, and of the 17 within
+            // these lines 6 and 4, by 3% on average (4M points 7563 and 8070,
+            // field of 300 spheres, outside them, 548 and 708; but 48 bodies
+            // 3472 and 3396). And beside matrices below 96 rows (order 4,
+            // 31,369 points 342, 374).
             P.eval_after_m2l = (P.m2l_form == 0 || P.m2l_form == 6) && P.r_pad >= 96 && b.load >= 5.0 && b.load >= 2.0 * b.chain;
             lap("m2l pair tiles and piece model");
             P.m2l_pieces_per_tile = kbest;
